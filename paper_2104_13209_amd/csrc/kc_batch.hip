@@ -150,7 +150,7 @@ BatchWs carve_batch(void* ws, const kc_batch* b, size_t* bytes) {
     w.task_tot = c.take<int>(static_cast<size_t>(nr));
     w.nactive = device_cus() * kLaneWavesPerCU;
     w.active = c.take<int>(static_cast<size_t>(w.nactive));
-    w.acc = c.take<unsigned long long>(kAccWords);
+    w.acc = c.take<unsigned long long>(kAccTotal);
     *bytes = c.bytes();
     return w;
 }
@@ -225,7 +225,7 @@ extern "C" KC_API int32_t kc_batch_count(const kc_batch* b, int32_t k, uint64_t*
     k_gid<<<grid_for(n), kBlock, 0, s>>>(n, w.perm, b->voff, G, w.gid);
     k_graph_bucket<<<grid_for(G), kBlock, 0, s>>>(G, b->voff, pl, w.bucket);
     k_fill_i32<<<grid_for(w.nactive), kBlock, 0, s>>>(w.active, -1, w.nactive);
-    k_fill_u64<<<1, kBlock, 0, s>>>(w.acc, 0ull, kAccWords);
+    k_fill_u64<<<1, kBlock, 0, s>>>(w.acc, 0ull, kAccTotal);
     KC_CHECK(hipGetLastError());
     if (m == 0) return KC_OK;
 

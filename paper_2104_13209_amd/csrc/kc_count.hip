@@ -25,6 +25,7 @@
 // last level the step adds popcount(Y); otherwise a non-empty Y is pushed.
 // Every lane keeps its own 64-bit partial count; wavefronts reduce them exactly
 // into a 128-bit device counter when they exit.
+#include <algorithm>
 #include <climits>
 #include <mutex>
 #include <new>
@@ -613,7 +614,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
     const int nroots = ec ? d->m : d->n;
     const int dm = bit_dmax(d->d_max);   // the on-chip kernels never see a wide root
     KC_CHECK(hipMemsetAsync(w.ctl, 0, CC_WORDS * sizeof(int), s));
-    unsigned long long init[kAccWords] = {};
+    unsigned long long init[kAccTotal] = {};
     init[0] = preload;
     for (int j = 0; j < kWidthLists; j++) init[6 + 4 * kWidthLists + 3 * j + 1] = ~0ull;   // min start of each list's timing
     KC_CHECK(hipMemcpyAsync(w.acc, init, sizeof(init), hipMemcpyHostToDevice, s));
@@ -646,7 +647,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             KC_CHECK(hipMemsetAsync(w.task_ctr, 0, sizeof(int) * static_cast<size_t>(nroots), s));
             KC_CHECK(hipMemsetAsync(w.task_tot, 0, sizeof(int) * static_cast<size_t>(nroots), s));
             KC_CHECK(hipMemsetAsync(w.qctl, 0, sizeof(int) * kQueueCtlWords * kWidthLists, s));
-            KC_CHECK(hipMemsetAsync(w.qready, 0, sizeof(int) * kQueueCap * kWidthLists, s));
+            KC_CHECK(hipMemsetAsync(w.qready, 0, sizeof(int) * kQueueCap * kQueueLists, s));
         }
         if (ec) {
             const int cap = dm > 1 ? dm : 1;
@@ -719,7 +720,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             L.cwords_ptr = w.acc + kAccCwords + lst;
             L.steal = L.pair && !(o && (o->flags & KC_OPT_NO_HANDOFF));
             L.qctl = w.qctl + kQueueCtlWords * lst;
-            L.qready = w.qready + static_cast<size_t>(kQueueCap) * lst;
+            L.qready = w.qready + static_cast<size_t>(kQueueCap) * queue_of(lst);
             L.qitems = w.qitems + (on_side ? static_cast<size_t>(kQueueCap) * kItemWords : 0);
             L.flags = w.ctl + CC_FLAGS;
             if (o) {
@@ -832,7 +833,8 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         if (!lane_path && dm <= kLightCap) KC_CHECK(hipEventRecord(pe->ev[2], s));
         KC_CHECK(hipEventRecord(pe->ev[3], s));
     }
-    KC_CHECK(hipMemcpyAsync(res, w.acc, kAccWords * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+    unsigned long long hacc[kAccTotal];
+    KC_CHECK(hipMemcpyAsync(hacc, w.acc, sizeof(hacc), hipMemcpyDeviceToHost, s));
     KC_CHECK(hipMemcpyAsync(hctl, w.ctl, CC_WORDS * sizeof(int), hipMemcpyDeviceToHost, s));
     int hq[kQueueCtlWords * kWidthLists] = {};
     const bool queued = lane_path && k >= (ec ? 3 : 2) + 4;
@@ -842,6 +844,15 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         KC_CHECK(hipMemcpyAsync(counts_out, w.counts, 2 * sizeof(unsigned long long) * counts_len,
                                 hipMemcpyDeviceToHost, s));
     KC_CHECK(hipStreamSynchronize(s));
+    std::copy(hacc, hacc + kAccWords, res);
+    for (int j = 0; j < kAccSlots; j++) {
+        const unsigned long long* x = hacc + kAccSlotBase + j * kAccSlotStride;
+        const unsigned __int128 a = (static_cast<unsigned __int128>(res[1]) << 64) | res[0];
+        const unsigned __int128 b = a + ((static_cast<unsigned __int128>(x[1]) << 64) | x[0]);
+        if (b < a) hctl[CC_FLAGS] |= kFlagBigBinom;   // the total passed 2^128
+        res[0] = static_cast<unsigned long long>(b);
+        res[1] = static_cast<unsigned long long>(b >> 64);
+    }
     if (prof) {
         KC_CHECK(hipEventElapsedTime(&prof->ms_classify, pe->ev[0], pe->ev[1]));
         if (lane_path) {   // heavy lists run first

@@ -11,6 +11,10 @@ constexpr int kLaneWavesPerCU = 32;    // grid cap of the lane-walk kernel (size
 constexpr int kWidthLists = 6;         // root lists by bitset words per row: 1, 2, 4, 8, 16, 32
 constexpr int kQueueCap = 16384;        // lane walk: ring slots for subtrees handed between wavefronts (power of 2)
 constexpr int kItemWords = 36;          // queue item: root slot, path length, 2 spare, 32 words of R
+// The lane walk's list 0 has no pair tasks and so no queue; list j >= 1 uses queue
+// j - 1, and the pivot launches use queues 0 (light) and 1 (heavy).
+constexpr int kQueueLists = kWidthLists - 1;
+constexpr int queue_of(int list) { return list > 0 ? list - 1 : 0; }
 constexpr int kQueueCtlWords = 8;       // per width list: head, tail, pending, rooting, hungry
 // subtree queue control words, and its bounds
 constexpr int Q_HEAD = 0, Q_TAIL = 1, Q_PENDING = 2, Q_ROOTING = 3, Q_HUNGRY = 4;
@@ -46,6 +50,14 @@ constexpr int kCancelEvery = 32;       // wavefront rounds (lane walk) or nodes 
 // cliques weighted by row words
 constexpr int kAccWords = 9 + 8 * kWidthLists;
 constexpr int kAccCwords = 9 + 7 * kWidthLists;
+// Final counts of the traversal wavefronts: kAccSlots {lo, hi} pairs on cache
+// lines of their own, after the words above; the host adds them up.  Atomics on
+// one address are served one after the other (11.6 ns each, measured), so 8192
+// wavefronts adding to a single pair took 95 us.
+constexpr int kAccSlots = 32;
+constexpr int kAccSlotStride = 16;                                   // u64 words: 128 bytes
+constexpr int kAccSlotBase = ((kAccWords + 15) / 16) * 16;
+constexpr int kAccTotal = kAccSlotBase + kAccSlots * kAccSlotStride;
 
 enum CountCtl {
     CC_LIGHT_N = 0,      // light root count
@@ -106,6 +118,63 @@ inline int s_cap_for(int d_max) { return ((d_max + 31) / 32) * 32 > kLightCap ? 
 // Words of one pivot stack level: I, P_orig, P_remaining (maxw each) + p, np, nh, pad.
 inline int piv_level_words(int maxw) { return 3 * maxw + 4; }
 
+// A wavefront's claims on a launch's roots (0 .. nroots - 1, in list order): chunks
+// of a sixteenth of its even share, at most `cap`.  The first chunk is fixed by the
+// wavefront's index, so a launch with no more chunks than wavefronts takes no
+// atomic at all; later ones come from the queue head, whose atomics are served one
+// after the other (11.6 ns each): with 8192 wavefronts that alone was 95 us of a
+// launch over 2000 roots.  The head is not looked at before it is claimed from:
+// plain loads of the contended line wait in the same queue (batch of 10,000
+// graphs: 37 -> 52 ms with such a look).
+//
+// SPREAD: the roots of a chunk lie a chunk count apart instead of side by side.
+// Lists end with the dense core's roots, so neighbours are heavy together: chunks
+// of neighbours took the per-vertex counts of a 200k-vertex power-law graph from
+// 5.2 to 23 ms.  Lists of small roots keep neighbours together, whose rows they share.
+struct RootClaims {
+    int next = 0, left = 0;         // claimed, unprocessed roots
+    int step = 1;                   // distance between the roots of a chunk
+    bool started = false;
+};
+
+// Claims the next chunk (roots c.next, c.next + c.step, ..., c.left of them;
+// wave-uniform); false when no root is left.  `head` is zero at launch; every lane
+// calls this.
+template <bool SPREAD>
+__device__ __forceinline__ bool claim_chunk(RootClaims& c, int* head, int nroots, int wave, int nwaves, int cap) {
+    int size = nroots / (16 * nwaves);
+    size = size < 1 ? 1 : size > cap ? cap : size;
+    const int chunks = (nroots + size - 1) / size;
+    int q = wave;
+    if (c.started) {
+        if (nwaves >= chunks) return false;
+        q = 0;
+        if (__lane_id() == 0) q = atomicAdd(head, 1);
+        q = nwaves + __shfl(q, 0);
+    }
+    c.started = true;
+    if (q >= chunks) return false;
+    if (SPREAD) {
+        c.next = q;
+        c.step = chunks;
+        c.left = (nroots - q + chunks - 1) / chunks;
+    } else {
+        c.next = q * size;
+        c.left = c.next + size < nroots ? size : nroots - c.next;
+    }
+    return true;
+}
+
+// The next root of this wavefront (wave-uniform), or -1 when none is left.
+template <bool SPREAD>
+__device__ __forceinline__ int claim_root(RootClaims& c, int* head, int nroots, int wave, int nwaves, int cap) {
+    if (c.left == 0 && !claim_chunk<SPREAD>(c, head, nroots, wave, nwaves, cap)) return -1;
+    const int r = c.next;
+    c.next += c.step;
+    c.left--;
+    return r;
+}
+
 struct CountWs {
     int* ctl;
     unsigned long long* acc;      // [lo, hi, light nodes, words, heavy nodes, words, then per width list nodes, words]
@@ -119,7 +188,7 @@ struct CountWs {
     int* task_tot;                // lane walk, pair tasks: total tasks + 1 per root (0 = unpublished)
     int* active;                  // lane walk: root slot owned by each wavefront (-1 = none), main + side
     int* qctl;                    // lane walk, subtree queue: kQueueCtlWords per width list
-    int* qready;                  // lane walk, subtree queue: slot sequence words, kQueueCap per width list
+    int* qready;                  // subtree queue: slot sequence words, kQueueCap per queue (see queue_of)
     unsigned int* qitems;         // lane walk, subtree queue: kItemWords per slot, main + side
     int* wide;                    // wide roots (d_max > KC_MAX_DMAX only)
     unsigned int* wslabs;         // wide roots: one slab per wavefront
@@ -137,7 +206,7 @@ inline CountWs carve_count(void* ws, const kc_dag* d, bool pivot, size_t* bytes)
     CountWs w{};
     const int nr = d->m > d->n ? d->m : d->n;
     w.ctl = c.take<int>(CC_WORDS);
-    w.acc = c.take<unsigned long long>(kAccWords);
+    w.acc = c.take<unsigned long long>(kAccTotal);
     w.light = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.heavy = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.task_ctr = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
@@ -145,7 +214,7 @@ inline CountWs carve_count(void* ws, const kc_dag* d, bool pivot, size_t* bytes)
     w.nactive = device_cus() * kLaneWavesPerCU;
     w.active = c.take<int>(2 * static_cast<size_t>(w.nactive));    // main and side stream
     w.qctl = c.take<int>(kQueueCtlWords * kWidthLists);
-    w.qready = c.take<int>(static_cast<size_t>(kQueueCap) * kWidthLists);
+    w.qready = c.take<int>(static_cast<size_t>(kQueueCap) * kQueueLists);
     w.qitems = c.take<unsigned int>(2 * static_cast<size_t>(kQueueCap) * kItemWords);   // main and side stream
     const int dm = bit_dmax(d->d_max);
     if (pivot) {

@@ -32,7 +32,11 @@ namespace kc {
 namespace lanewalk {
 
 constexpr int kPairChunk = 64;    // pair tasks claimed per global atomic
-constexpr int kRootChunk = 8;     // vertex-task roots claimed per global atomic
+// Most roots claimed at once: vertex-task lists have many small roots, pair-task
+// lists few large ones (8 at a time left wavefronts with several dense-core
+// roots each: k = 10 on the 1M-vertex power-law graph 460 -> 525 ms).
+constexpr int kRootChunk = 32;
+constexpr int kPairRootChunk = 1;
 constexpr int kInner = 8;         // lane-local steps per wavefront-level round
 constexpr int kStealMax = 8;      // subtrees handed over per look
 
@@ -50,7 +54,7 @@ struct LaneParams {
     int* task_ctr;                  // pair mode: per-root claimed-task counters
     int* task_tot;                  // pair mode: per-root task totals + 1 (0 = not published)
     int* active;                    // pair mode: root slot owned by each wavefront, -1 if none
-    unsigned long long* acc;        // [lo, hi]
+    unsigned long long* acc;        // kAccTotal words (counts go to the slots)
     unsigned long long* stats;      // [nodes, words]
     unsigned long long* iters;      // [traversal loop iterations per wavefront, lane expansions], summed
     unsigned long long* timing;     // [sum of wavefront busy ticks, min start, max end]
@@ -624,24 +628,18 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
     const unsigned long long t_begin = STATS ? __builtin_amdgcn_s_memrealtime() : 0ull;
     if (steal && lane == 0) atomicAdd(&q[Q_ROOTING], 1);    // in the root phase
     bool helping = steal && P.helper;               // helpers own no roots (and no registry entry)
-    int rq = 0, rq_end = 0;                         // claimed, unprocessed root range
-    int claims = 0;                                 // root claims since the last cancel poll
-    constexpr int RC = PAIR ? 1 : kRootChunk;
+    RootClaims rc;
+    int claims = 0;                                 // roots walked since the last cancel poll
 
     // ---------------------------------------------- root phase
     for (;;) {
         int slot = -1;
         if (!helping) {
-            if (rq == rq_end) {
-                int r = 0;
-                if (lane == 0) r = atomicAdd(P.head, RC);
-                r = __shfl(r, 0);
-                rq = r < nroots ? r : nroots;
-                rq_end = r + RC < nroots ? r + RC : nroots;
+            slot = claim_root<PAIR>(rc, P.head, nroots, blockIdx.x, nwaves, PAIR ? kPairRootChunk : kRootChunk);
+            if (slot < 0) {
+                if (PAIR) helping = true;
+                else break;
             }
-            if (rq < rq_end) slot = rq++;
-            else if (PAIR) helping = true;
-            else break;
         }
         if (PAIR && helping) {
             // join the in-progress root with the most unclaimed pair tasks
@@ -792,7 +790,10 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
 
     unsigned long long lo, hi;
     wave_sum_u128(acc, lo, hi);
-    if (lane == 0) atomic_add_u128(P.acc, P.acc + 1, lo, hi);
+    if (lane == 0) {
+        unsigned long long* slot = P.acc + kAccSlotBase + kAccSlotStride * (blockIdx.x % kAccSlots);
+        atomic_add_u128(slot, slot + 1, lo, hi);
+    }
     if (STATS) {
         nodes = wave_sum(nodes);
         wsum = wave_sum(wsum);

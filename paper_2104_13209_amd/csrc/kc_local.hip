@@ -100,27 +100,36 @@ __global__ void __launch_bounds__(64) k_local(LocalParams P) {
     const int p0 = EC ? 3 : 2;                           // path length of a task's first node
     const unsigned long long lt = lanemask_lt();
 
+    RootClaims rc;
+    unsigned long long todo = 0;                         // bits: roots of the claimed chunk
     for (;;) {
-        int root = 0;
-        if (lane == 0) {
-            root = atomicAdd(P.head, 1);
-            if (P.cancel && root < P.nroots && cancel_requested(P.cancel)) {
-                atomicOr(P.flags, kFlagCanceled);
-                root = P.nroots;
+        if (todo == 0ull) {
+            if (!claim_chunk<true>(rc, P.head, P.nroots, blockIdx.x, gridDim.x, 64)) break;
+            // the size bound of S decides before any extraction: a lane per root
+            int bound = -1;
+            if (lane < rc.left) {
+                const int r = rc.next + lane * rc.step;
+                if (EC) {
+                    const int u = P.src[r], v = P.col[r];
+                    const int du = P.row_ptr[u + 1] - P.row_ptr[u], dv = P.row_ptr[v + 1] - P.row_ptr[v];
+                    bound = du - 1 < dv ? du - 1 : dv;
+                } else {
+                    bound = P.row_ptr[r + 1] - P.row_ptr[r];
+                }
             }
+            todo = __ballot(bound >= P.need && bound >= 0);
+            continue;
         }
-        root = __shfl(root, 0);
-        if (root >= P.nroots) break;
-        // the size bound of S decides before any extraction
-        int bound;
-        if (EC) {
-            const int u = P.src[root], v = P.col[root];
-            const int du = P.row_ptr[u + 1] - P.row_ptr[u], dv = P.row_ptr[v + 1] - P.row_ptr[v];
-            bound = du - 1 < dv ? du - 1 : dv;
-        } else {
-            bound = P.row_ptr[root + 1] - P.row_ptr[root];
+        if (P.cancel) {
+            int c = 0;
+            if (lane == 0 && cancel_requested(P.cancel)) {
+                atomicOr(P.flags, kFlagCanceled);
+                c = 1;
+            }
+            if (__shfl(c, 0)) break;
         }
-        if (bound < P.need) continue;
+        const int root = rc.next + (__ffsll(static_cast<long long>(todo)) - 1) * rc.step;
+        todo &= todo - 1ull;
         extract_set<1, EC>(root, P.row_ptr, P.col, P.src, lane, S, &ctl[1]);
         const int s = ctl[1];
         if (s < P.need) continue;

@@ -29,6 +29,9 @@
 namespace kc {
 namespace {
 
+// Most roots claimed at once: light roots (at most 64 candidates), heavy ones.
+constexpr int kPivRootChunkLight = 4, kPivRootChunkHeavy = 1;
+
 struct PivParams {
     int k;
     int s_cap;
@@ -40,7 +43,7 @@ struct PivParams {
     const int* __restrict__ nroots;
     int* head;
     int* flags;
-    unsigned long long* acc;                 // [lo, hi]
+    unsigned long long* acc;                 // kAccTotal words (counts go to the slots)
     unsigned long long* counts;              // count-all: {lo, hi} per size
     const unsigned long long* __restrict__ binom;
     const unsigned char* __restrict__ big;
@@ -227,6 +230,7 @@ __global__ void __launch_bounds__(64 * WPB) k_piv(PivParams P) {
     }
     if (steal && lane == 0) atomicAdd(&q[Q_ROOTING], 1);
     bool roots_done = false, hungry = false, canceled = false;
+    RootClaims rc;
     int cur = -1, chk = 0, cpoll = 0;                 // root whose S and rows are in LDS
     for (;;) {
         int slot = -1;
@@ -234,12 +238,9 @@ __global__ void __launch_bounds__(64 * WPB) k_piv(PivParams P) {
         unsigned int I = 0, Po = 0, Pr = 0;
         int np = 0, nh = nh_root, level = 0, p = 0;
         if (!roots_done) {
-            int root = 0;
-            if (lane == 0) root = atomicAdd(P.head, 1);
-            root = __shfl(root, 0);
-            if (root < nroots) {
-                slot = root;
-            } else {
+            slot = claim_root<true>(rc, P.head, nroots, blockIdx.x * WPB + wv, gridDim.x * WPB,
+                              MAXW <= 2 ? kPivRootChunkLight : kPivRootChunkHeavy);
+            if (slot < 0) {
                 roots_done = true;
                 if (!steal) break;
                 if (lane == 0) __hip_atomic_fetch_add(&q[Q_ROOTING], -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -543,7 +544,8 @@ __global__ void __launch_bounds__(64 * WPB) k_piv(PivParams P) {
 
     // flush
     if (!ALL) {
-        if (lane == 0 && atomic_add_u128(P.acc, P.acc + 1, acc_lo, acc_hi)) ovf = 1;
+        unsigned long long* slot = P.acc + kAccSlotBase + kAccSlotStride * ((blockIdx.x * WPB + wv) % kAccSlots);
+        if (lane == 0 && atomic_add_u128(slot, slot + 1, acc_lo, acc_hi)) ovf = 1;
     } else {
         wave_sync_lds();
         for (int i = lane; i <= cap; i += 64) {
