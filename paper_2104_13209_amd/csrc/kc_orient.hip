@@ -10,13 +10,9 @@
 //   filter    per vertex, keep neighbours with a larger new id; out-degree
 //             histogram, exclusive scan -> row_ptr (the paper's histogram + scan)
 //   compact   gather each kept row, sort it by new id, write col and the COO src
-#include <hip/hip_cooperative_groups.h>
-
 #include <climits>
 
 #include "kc_internal.h"
-
-namespace cg = cooperative_groups;
 
 namespace kc {
 namespace {
@@ -37,12 +33,16 @@ enum Ctl {
     CTL_ZEROS = 6,     // zero count of the current radix pass
     CTL_SIZE0 = 8,     // peel frontier sizes, ring of 3 (8, 9, 10)
     CTL_MIN = 11,      // peel level minimum
-    CTL_HSIZE0 = 12,   // peel heavy-frontier sizes, ring of 3 (12, 13, 14)
+    CTL_LEVEL = 12,    // peel: current level
+    CTL_CORE = 13,     // peel: vertices left for the one-workgroup rounds
+    CTL_DONE = 14,     // peel: the whole-device rounds ended regularly
+    CTL_CORE_AT = 15,  // peel: entries of the compacted rows
     CTL_CL_SIZE0 = 8,  // colouring: light frontier sizes, ring of 3 (8, 9, 10; not used with the peel)
     CTL_CL_HSIZE0 = 12,// colouring: heavy frontier sizes, ring of 3 (12, 13, 14)
     CTL_AD_LIVE = 16,  // approximate degeneracy: vertices left
     CTL_AD_SUM = 18,   // approximate degeneracy: their degree sum (u64 over words 18, 19)
-    CTL_WORDS = 20
+    CTL_BAR = 32,      // peel: barrier arrivals, on a cache line of their own
+    CTL_WORDS = 64
 };
 
 // ------------------------------------------------------------ validation
@@ -94,182 +94,447 @@ __global__ void __launch_bounds__(kBlock) k_degree_key(int n, const int* __restr
     if ((threadIdx.x & 63) == 0) atomicMax(&ctl[CTL_MAXKEY], mx);
 }
 
-// Appends the flagged lanes' values to list[] with one atomic per wavefront.
-__device__ __forceinline__ void append_wave(bool flag, int v, int* list, int* size, int lane) {
-    const unsigned long long m = __ballot(flag);
-    if (m == 0ull) return;
-    int base = 0;
-    if (lane == 0) base = atomicAdd(size, __popcll(m));
-    base = __shfl(base, 0);
-    if (flag) list[base + __popcll(m & lanemask_lt())] = v;
+// --------------------------------------------------- degeneracy order (peeling)
+//
+// Level-synchronous peeling (the paper only states that its k-core decomposition
+// runs on the GPU; this schedule is ours).  Level c starts when no live vertex has
+// degree <= c - 1; its first frontier is every live vertex of degree <= c.  Each
+// round removes the whole frontier (key = round) and decrements its neighbours; a
+// neighbour whose degree falls from c + 1 to c joins the next frontier.  When a
+// round leaves an empty frontier the next level is the minimum live degree.  A
+// vertex removed in round r at level c had at most c live neighbours at the start of
+// round r, and its out-neighbours under the (round, id) order are among them, so
+// the out-degree is bounded by the degeneracy (the largest level).
+//
+// No liveness check is needed anywhere: degrees of removed vertices never exceed
+// the level at which they left, so they never fall "from c + 1", and between
+// levels the live vertices are exactly those of degree > c.
+//
+// The rounds are serial (1,941 of them on a 1M-vertex power-law graph of
+// degeneracy 286) and bound by latency: a barrier and a chain of dependent accesses
+// each.  All but the first few hundred of them happen when few vertices are left, so
+// the work is split there: k_peel removes vertices with the whole device until at
+// most kCoreCap are left, the rows among those are compacted to 16-bit local ids
+// (k_core_list, k_core_rows), and k_core_peel finishes in one workgroup
+// with the degrees and the queue in LDS, where a round costs a block barrier and
+// one row read.  Measured on that graph (orientation without validation, us): 35,100
+// with every round behind a cooperative-groups grid barrier, of which the barriers
+// alone are 8.7 us each at 61 blocks (their fences write back and invalidate
+// every L2).
+
+constexpr int kPeelBlock = 1024;
+constexpr int kCoreCap = 26000;   // 6 bytes of LDS each, of 160 KB
+constexpr int kCoreLds = 6 * kCoreCap + 8;
+constexpr int kPeelSpins = 1 << 22;
+
+template <class T>
+__device__ __forceinline__ void st_agent(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Frontier of one peeling round, split by row length: light vertices (rows of
-// at most kHeavyRow entries) are walked by one wavefront each, the rows of heavy
-// vertices are cut into 64-entry chunks that all wavefronts share.
-constexpr int kHeavyRow = 128;
-struct Frontier {
-    int* light;
-    int* heavy;
-    int* nlight;
-    int* nheavy;
+// Grid barrier of a cooperative launch (all blocks co-resident) for data that
+// blocks exchange only through agent-scope atomic loads, stores and updates: those
+// are served past the XCDs' L2s, so it is enough that they have been performed
+// (s_waitcnt) when the block arrives; no cache is written back or invalidated.
+// 1.3 us at 64 blocks (cooperative groups: 8.7).  False once a wait ran out, after
+// which every block leaves.
+__device__ __forceinline__ bool peel_barrier(int* bar, int& epoch, int* shared_ok) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    epoch++;
+    if (threadIdx.x == 0) {
+        const int want = epoch * static_cast<int>(gridDim.x);
+        __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int spins = 0;
+        while (ld_acquire(bar) < want && ++spins < kPeelSpins) __builtin_amdgcn_s_sleep(1);
+        *shared_ok = spins < kPeelSpins;
+    }
+    __syncthreads();
+    return *shared_ok != 0;
+}
+
+// The next frontier as one block gathers it: vertices go to an LDS buffer and reach
+// the global list by one atomic per block and round (peel_flush).  An atomic per
+// appending wavefront on the list's size bound the whole kernel: some 700,000 of
+// them at 11.6 ns, 8.6 ms.  What the buffer cannot hold is appended directly.
+constexpr int kPeelBuf = 16384;
+
+struct PeelNext {
+    int* list;    // global list and its size
+    int* size;
+    int* buf;     // LDS
+    int* count;
 };
 
-// Appends flagged vertices to the light or heavy list by row length.
-__device__ __forceinline__ void append_split(bool flag, int v, const int* __restrict__ row_ptr, const Frontier& f,
-                                             int lane) {
-    bool heavy = false;
-    if (flag) heavy = row_ptr[v + 1] - row_ptr[v] > kHeavyRow;
-    append_wave(flag && !heavy, v, f.light, f.nlight, lane);
-    append_wave(flag && heavy, v, f.heavy, f.nheavy, lane);
+__device__ __forceinline__ void peel_push(bool flag, int v, const PeelNext& nx, int lane) {
+    const unsigned long long m = __ballot(flag);
+    if (m == 0ull) return;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(nx.count, __popcll(m));
+    at = __shfl(at, 0) + __popcll(m & lanemask_lt());
+    if (flag && at < kPeelBuf) nx.buf[at] = v;
+    if (flag && at >= kPeelBuf) st_agent(&nx.list[atomicAdd(nx.size, 1)], v);
 }
 
-// One entry of the row being peeled: a live neighbour loses one degree and joins
-// the next frontier when it drops to the level c.  A stale read of a vertex
-// removed earlier only decrements a dead degree, which never equals c + 1.
-__device__ __forceinline__ void peel_entry(int j, int e, int c, const int* __restrict__ row_ptr,
-                                           const int* __restrict__ col, int* deg, const int* rnd,
-                                           const Frontier& nx, int lane) {
-    bool hit = false;
-    int w = 0;
-    if (j < e) {
-        w = col[j];
-        if (ld_acquire(&rnd[w]) < 0) hit = atomicSub(&deg[w], 1) == c + 1;
-    }
-    append_split(hit, w, row_ptr, nx, lane);
+// Moves the block's buffer to the global list and empties it; all threads call it.
+__device__ __forceinline__ void peel_flush(const PeelNext& nx, int* base) {
+    __syncthreads();
+    const int cnt = *nx.count < kPeelBuf ? *nx.count : kPeelBuf;
+    if (cnt == 0) return;
+    if (threadIdx.x == 0) *base = atomicAdd(nx.size, cnt);
+    __syncthreads();
+    for (int i = threadIdx.x; i < cnt; i += blockDim.x) st_agent(&nx.list[*base + i], nx.buf[i]);
+    if (threadIdx.x == 0) *nx.count = 0;
 }
 
-// One peeling round: the frontier's vertices get round r and their live
-// neighbours lose one degree each.  Light vertices: wavefront `wave` of nwaves
-// takes entries wave, wave + nwaves, ...  Heavy vertices, 64 at a time: every
-// wavefront reads their row lengths, numbers the 64-entry chunks of all their
-// rows, and takes chunks wave, wave + nwaves, ...
-__device__ __forceinline__ void peel_round(int r, int c, const int* cur, int fsize, const int* hcur, int hsize,
-                                           const Frontier& nx, const int* __restrict__ row_ptr,
-                                           const int* __restrict__ col, int* deg, int* rnd, int wave, int nwaves,
-                                           int lane) {
-    for (int fi = wave; fi < fsize; fi += nwaves) {
-        const int v = ld_acquire(&cur[fi]);
-        if (lane == 0) rnd[v] = r;
-        const int b = row_ptr[v], e = row_ptr[v + 1];
-        for (int j0 = b; j0 < e; j0 += 64) peel_entry(j0 + lane, e, c, row_ptr, col, deg, rnd, nx, lane);
-    }
-    for (int h0 = 0; h0 < hsize; h0 += 64) {
-        const int hi = h0 + lane;
-        int v = 0, b = 0, e = 0, nch = 0;
-        if (hi < hsize) {
-            v = ld_acquire(&hcur[hi]);
-            b = row_ptr[v];
-            e = row_ptr[v + 1];
-            nch = (e - b + 63) >> 6;
-            if (wave == 0) rnd[v] = r;
-        }
-        int incl = nch;                          // inclusive prefix of chunk counts
+constexpr int kPeelLongRow = 128;
+
+// Row entries j, j + stride, ... below e lose one degree each; those that reach the
+// level c join the next frontier.  The wavefront makes as many steps as its longest
+// share: `span` entries of 0, or from `first` to e.  Four loads, then four updates,
+// are in flight per lane.
+__device__ __forceinline__ void peel_row(int j, int first, int e, int stride, int c, const int* __restrict__ col,
+                                         int* deg, const PeelNext& nx, int lane, int span = -1) {
+    const int len = span >= 0 ? span : e - first;
+    for (int t = 0; t < len; t += 4 * stride, j += 4 * stride) {
+        int w[4], old[4];
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int y = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += y;
-        }
-        const int excl = incl - nch;
-        const int total = __shfl(incl, 63);
-        for (int q = wave; q < total; q += nwaves) {
-            // owner: the last lane whose exclusive prefix is <= q
-            const int owner = __popcll(__ballot(hi < hsize && excl <= q)) - 1;
-            const int ob = __shfl(b, owner), oe = __shfl(e, owner), ox = __shfl(excl, owner);
-            peel_entry(ob + (q - ox) * 64 + lane, oe, c, row_ptr, col, deg, rnd, nx, lane);
-        }
+        for (int q = 0; q < 4; q++) w[q] = j + q * stride < e ? col[j + q * stride] : -1;
+#pragma unroll
+        for (int q = 0; q < 4; q++) old[q] = w[q] >= 0 ? atomicSub(&deg[w[q]], 1) : 0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) peel_push(w[q] >= 0 && old[q] == c + 1, w[q], nx, lane);
     }
 }
 
-// Degeneracy order by level-synchronous peeling (the paper only states that its
-// k-core decomposition runs on the GPU; this schedule is ours).
-//
-// Level c starts when no live vertex has degree <= c - 1; its first frontier is
-// every live vertex of degree <= c.  Each round removes the whole frontier
-// (rnd[v] = round), decrements live neighbours, and a neighbour whose degree
-// falls from c + 1 to c joins the next frontier.  When a round leaves an empty
-// frontier the next level is the minimum live degree.  A vertex removed in round
-// r at level c had at most c live neighbours at the start of round r, and its
-// out-neighbours under the (round, id) order are among them, so the out-degree
-// is bounded by the degeneracy (the largest level).
-//
-// One pass collects both the vertices of degree <= c + 1 and the minimum live
-// degree, since the next level is almost always c + 1; a second pass runs only
-// when no live vertex has that degree.  Frontier appends take one atomic per
-// wavefront.
-__global__ void __launch_bounds__(kBlock) k_peel(int n, const int* __restrict__ row_ptr,
-                                                const int* __restrict__ col, int* deg, int* rnd,
-                                                int* fr0, int* fr1, int* hf0, int* hf1, int* val, int* ctl) {
-    cg::grid_group grid = cg::this_grid();
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nth = gridDim.x * blockDim.x;
+// The whole-device rounds: until at most `keep` vertices are left.  A frontier of
+// f vertices gets the nwaves / f wavefronts (at most 64) that there are for each,
+// so that the hubs' long rows are shared while frontiers are small.  Leaves the
+// level in CTL_LEVEL, the rounds so far in CTL_ROUNDS, the degrees of the vertices
+// left (their live neighbours) in deg[], and key[v] = -1 for those.
+__global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int* __restrict__ row_ptr,
+                                                    const int* __restrict__ col, int* deg, int* key, int* fr0,
+                                                    int* fr1, int* val, int* ctl) {
+    __shared__ int ok, count, base, least;
+    __shared__ int buf[kPeelBuf];
+    const int tid = blockIdx.x * kPeelBlock + threadIdx.x;
+    const int nth = gridDim.x * kPeelBlock;
     const int lane = threadIdx.x & 63;
     const int wave = tid >> 6;
     const int nwaves = nth >> 6;
+    int* bar = ctl + CTL_BAR;
+    int epoch = 0;
 
     for (int v = tid; v < n; v += nth) {
-        deg[v] = row_ptr[v + 1] - row_ptr[v];
-        rnd[v] = -1;
+        st_agent(&deg[v], row_ptr[v + 1] - row_ptr[v]);
+        st_agent(&key[v], -1);   // written again from another XCD: no copy may stay in this one's L2
         val[v] = v;
     }
-    if (tid == 0) {
-        ctl[CTL_SIZE0] = ctl[CTL_SIZE0 + 1] = ctl[CTL_SIZE0 + 2] = 0;
-        ctl[CTL_HSIZE0] = ctl[CTL_HSIZE0 + 1] = ctl[CTL_HSIZE0 + 2] = 0;
-        ctl[CTL_MIN] = INT_MAX;
+    if (tid == 0) st_agent(&ctl[CTL_MIN], INT_MAX);
+    if (threadIdx.x == 0) {
+        count = 0;
+        least = INT_MAX;
     }
-    grid.sync();
+    if (!peel_barrier(bar, epoch, &ok)) return;
 
     int removed = 0, r = 0, c = -1, degen = 0;
-    while (removed < n) {
+    while (n - removed > keep) {
         const int* cur = (r & 1) ? fr1 : fr0;
-        const int* hcur = (r & 1) ? hf1 : hf0;
-        const Frontier nx{(r & 1) ? fr0 : fr1, (r & 1) ? hf0 : hf1, &ctl[CTL_SIZE0 + (r + 1) % 3],
-                          &ctl[CTL_HSIZE0 + (r + 1) % 3]};
+        const PeelNext nx{(r & 1) ? fr0 : fr1, &ctl[CTL_SIZE0 + (r + 1) % 3], buf, &count};
         const int fsize = ld_acquire(&ctl[CTL_SIZE0 + r % 3]);
-        const int hsize = ld_acquire(&ctl[CTL_HSIZE0 + r % 3]);
-        if (fsize + hsize == 0) {
-            // Level change, as an empty round r: the next frontier is collected
-            // into the next lists (no block reads those while others may still be
-            // reading csize above), then round r + 1 peels it.  One pass takes
-            // the live vertices of degree <= c + 1 and the minimum live degree.
-            if (tid == 0) ctl[CTL_SIZE0 + (r + 2) % 3] = ctl[CTL_HSIZE0 + (r + 2) % 3] = 0;
+        if (tid == 0) st_agent(&ctl[CTL_SIZE0 + (r + 2) % 3], 0);   // only the finished round r - 1 read it
+        if (fsize == 0) {
+            // Level change, as an empty round r: one pass takes the live vertices of
+            // degree c + 1 and the minimum live degree; a second one runs only when
+            // no live vertex has that degree.
             int mn = INT_MAX;
-            for (int b0 = tid - lane; b0 < n; b0 += nth) {
-                const int v = b0 + lane;
-                bool in = false;
-                if (v < n && ld_acquire(&rnd[v]) < 0) {
-                    const int d = ld_acquire(&deg[v]);
-                    mn = d < mn ? d : mn;
-                    in = d <= c + 1;
+            for (int b0 = tid - lane; b0 < n; b0 += 4 * nth) {
+                int d[4];
+#pragma unroll
+                for (int q = 0; q < 4; q++) d[q] = b0 + q * nth + lane < n ? ld_acquire(&deg[b0 + q * nth + lane]) : -1;
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    if (d[q] > c) mn = d[q] < mn ? d[q] : mn;
+                    peel_push(d[q] == c + 1, b0 + q * nth + lane, nx, lane);
                 }
-                append_split(in, v, row_ptr, nx, lane);
             }
             mn = wave_min(mn);
-            if (lane == 0 && mn != INT_MAX) atomicMin(&ctl[CTL_MIN], mn);
-            grid.sync();
-            if (ld_acquire(nx.nlight) + ld_acquire(nx.nheavy) > 0) {
-                c = c + 1;          // the minimum live degree is c + 1
-            } else {
-                c = ld_acquire(&ctl[CTL_MIN]);
+            if (lane == 0 && mn != INT_MAX) atomicMin(&least, mn);
+            peel_flush(nx, &base);
+            if (threadIdx.x == 0) {
+                if (least != INT_MAX) atomicMin(&ctl[CTL_MIN], least);
+                least = INT_MAX;
+            }
+            if (!peel_barrier(bar, epoch, &ok)) return;
+            const int old = c;
+            c = ld_acquire(&ctl[CTL_MIN]);
+            if (c != old + 1) {
                 for (int b0 = tid - lane; b0 < n; b0 += nth) {
                     const int v = b0 + lane;
-                    const bool in = v < n && ld_acquire(&rnd[v]) < 0 && ld_acquire(&deg[v]) <= c;
-                    append_split(in, v, row_ptr, nx, lane);
+                    peel_push(v < n && ld_acquire(&deg[v]) == c, v, nx, lane);
                 }
-                grid.sync();
             }
-            if (tid == 0) ctl[CTL_MIN] = INT_MAX;   // every read of it is behind the last barrier
+            if (c != old + 1) peel_flush(nx, &base);
+            if (!peel_barrier(bar, epoch, &ok)) return;
+            if (tid == 0) st_agent(&ctl[CTL_MIN], INT_MAX);   // every read of it is behind the last barrier
             degen = c > degen ? c : degen;
             r++;
             continue;
         }
-        if (tid == 0) ctl[CTL_SIZE0 + (r + 2) % 3] = ctl[CTL_HSIZE0 + (r + 2) % 3] = 0;
-        peel_round(r, c, cur, fsize, hcur, hsize, nx, row_ptr, col, deg, rnd, wave, nwaves, lane);
-        removed += fsize + hsize;
+        if (fsize <= nwaves) {
+            int parts = nwaves / fsize;
+            parts = parts > 64 ? 64 : parts;
+            const int units = fsize * parts;
+            for (int q = wave; q < units; q += nwaves) {
+                const int part = q / fsize;
+                const int v = ld_acquire(&cur[q - part * fsize]);
+                if (part == 0 && lane == 0) st_agent(&key[v], r);
+                const int b = row_ptr[v], e = row_ptr[v + 1];
+                peel_row(b + part * 64 + lane, b + part * 64, e, parts * 64, c, col, deg, nx, lane);
+            }
+        } else {
+            // more vertices than wavefronts: a wavefront takes up to 64 at a time (their
+            // row bounds in one load each) and walks eight short rows at once, eight
+            // lanes each; rows beyond kPeelLongRow entries then get all its lanes
+            int per = (fsize + nwaves - 1) / nwaves;
+            per = per > 64 ? 64 : (per + 7) & ~7;
+            for (int f0 = wave * per; f0 < fsize; f0 += nwaves * per) {
+                int v = 0, b = 0, e = 0;
+                if (lane < per && f0 + lane < fsize) {
+                    v = ld_acquire(&cur[f0 + lane]);
+                    st_agent(&key[v], r);
+                    b = row_ptr[v];
+                    e = row_ptr[v + 1];
+                }
+                const bool is_long = e - b > kPeelLongRow;
+                const unsigned long long longs = __ballot(is_long);
+                for (int g = 0; g < per; g += 8) {
+                    const int from = g + (lane >> 3);
+                    const int gb = __shfl(b, from), ge = __shfl(is_long ? b : e, from);
+                    const int len = wave_max(ge - gb);
+                    peel_row(gb + (lane & 7), 0, ge, 8, c, col, deg, nx, lane, len);
+                }
+                for (unsigned long long m = longs; m; m &= m - 1ull) {
+                    const int from = __ffsll(static_cast<long long>(m)) - 1;
+                    const int gb = __shfl(b, from), ge = __shfl(e, from);
+                    peel_row(gb + lane, gb, ge, 64, c, col, deg, nx, lane);
+                }
+            }
+        }
+        peel_flush(nx, &base);
+        removed += fsize;
         r++;
-        grid.sync();
+        if (!peel_barrier(bar, epoch, &ok)) return;
     }
     if (tid == 0) {
+        ctl[CTL_DEGEN] = degen;
+        ctl[CTL_LEVEL] = c;
+        ctl[CTL_ROUNDS] = r;
+        ctl[CTL_MAXKEY] = r > 0 ? r - 1 : 0;
+        ctl[CTL_DONE] = 1;
+    }
+}
+
+// Graphs of at most kCoreCap vertices start in the one-workgroup peel.
+__global__ void __launch_bounds__(kBlock) k_peel_init(int n, const int* __restrict__ row_ptr, int* deg, int* key,
+                                                     int* val, int* ctl) {
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
+        deg[v] = row_ptr[v + 1] - row_ptr[v];
+        key[v] = -1;
+        val[v] = v;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl[CTL_LEVEL] = -1;
+        ctl[CTL_DONE] = 1;
+    }
+}
+
+// Local ids of the vertices left (cid[v], -1 for the others; list[id] = v) and
+// where their rows start among the compacted ones.  Ids and rows are handed out
+// block by block in any order: only the queue's order depends on it, and the keys
+// do not.  span[id] = {start, live degree}.
+__global__ void __launch_bounds__(kPeelBlock) k_core_list(int n, const int* __restrict__ key,
+                                                         const int* __restrict__ deg, int* cid, int* list, int2* span,
+                                                         int* ctl) {
+    __shared__ int cnt[kPeelBlock / 64], sum[kPeelBlock / 64];
+    __shared__ int base_id, base_at;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int v = blockIdx.x * kPeelBlock + threadIdx.x;
+    const bool live = v < n && key[v] < 0;
+    const int d = live && deg[v] > 0 ? deg[v] : 0;
+    const int room = (d + 3) & ~3;               // rows start at 8-byte boundaries
+    const unsigned long long m = __ballot(live);
+    int inc = room;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += y;
+    }
+    if (lane == 63) {
+        cnt[w] = __popcll(m);
+        sum[w] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int run = 0, at = 0;
+        for (int i = 0; i < kPeelBlock / 64; i++) {
+            const int t = cnt[i], u = sum[i];
+            cnt[i] = run;
+            sum[i] = at;
+            run += t;
+            at += u;
+        }
+        base_id = run ? atomicAdd(&ctl[CTL_CORE], run) : 0;
+        base_at = at ? atomicAdd(&ctl[CTL_CORE_AT], at) : 0;
+    }
+    __syncthreads();
+    int id = -1;
+    if (live) {
+        id = base_id + cnt[w] + __popcll(m & lanemask_lt());
+        if (id < kCoreCap) {
+            list[id] = v;
+            span[id] = make_int2(base_at + sum[w] + inc - room, d);
+        } else {
+            id = -1;
+        }
+    }
+    if (v < n) cid[v] = id;
+}
+
+// One wavefront per vertex left: its neighbours among those left, as local ids,
+// filled up to a multiple of four with the id kCoreCap, which stands for no vertex.
+__global__ void __launch_bounds__(kBlock) k_core_rows(const int* __restrict__ row_ptr,
+                                                     const int* __restrict__ col, const int* __restrict__ cid,
+                                                     const int* __restrict__ list, const int2* __restrict__ span,
+                                                     unsigned short* rows, const int* ctl) {
+    const int lane = threadIdx.x & 63;
+    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int nwaves = (gridDim.x * blockDim.x) >> 6;
+    const int L = ctl[CTL_CORE] < kCoreCap ? ctl[CTL_CORE] : kCoreCap;
+    for (int i = wave; i < L; i += nwaves) {
+        const int v = list[i];
+        const int b = row_ptr[v], e = row_ptr[v + 1];
+        int pos = span[i].x;
+        const int end = pos + ((span[i].y + 3) & ~3);
+        for (int j0 = b; j0 < e; j0 += 256) {
+            int x[4], id[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) x[q] = j0 + 64 * q + lane < e ? col[j0 + 64 * q + lane] : -1;
+#pragma unroll
+            for (int q = 0; q < 4; q++) id[q] = x[q] >= 0 ? cid[x[q]] : -1;
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const unsigned long long m = __ballot(id[q] >= 0);
+                const int at = pos + __popcll(m & lanemask_lt());
+                if (id[q] >= 0 && at < end) rows[at] = static_cast<unsigned short>(id[q]);
+                pos += __popcll(m);
+            }
+        }
+        if (pos + lane < end) rows[pos + lane] = static_cast<unsigned short>(kCoreCap);
+    }
+}
+
+// The remaining rounds by one workgroup: degrees and the queue (every vertex once, in
+// order of removal; a round is the segment [head, tail)) are in LDS.  One compute
+// unit's instruction issue bounds it (a round has some 28 rows of 300 entries), so
+// degrees are whole words and rows are padded: an entry costs about five instructions
+// instead of 14 with 16-bit degrees, bounds tests and an early exit each (which
+// took 5.7 ms on the 1M-vertex graph although they held half as many vertices again).
+__global__ void __launch_bounds__(kPeelBlock) k_core_peel(const int2* __restrict__ span,
+                                                         const unsigned short* __restrict__ rows,
+                                                         const int* __restrict__ list, int* round_of, int* key,
+                                                         int* ctl) {
+    extern __shared__ int core_lds[];
+    __shared__ int s_tail, s_min;
+    int* deg = core_lds;                                                       // kCoreCap + 1
+    unsigned short* queue = reinterpret_cast<unsigned short*>(core_lds + kCoreCap + 1);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int NW = kPeelBlock / 64;
+    const int L = ctl[CTL_CORE] < kCoreCap ? ctl[CTL_CORE] : kCoreCap;
+    for (int i = t; i < L; i += kPeelBlock) deg[i] = span[i].y;
+    int c = ctl[CTL_LEVEL], r = ctl[CTL_ROUNDS], degen = ctl[CTL_DEGEN];
+    if (t == 0) {
+        deg[kCoreCap] = INT_MAX;   // the padding: never falls to a level
+        s_tail = 0;
+        s_min = INT_MAX;
+    }
+    __syncthreads();
+    // every vertex is queued once; the bound only matters for malformed graphs that
+    // the caller chose not to have validated
+    auto push = [&](int v) {
+        const int at = atomicAdd(&s_tail, 1);
+        if (at < kCoreCap) queue[at] = static_cast<unsigned short>(v);
+    };
+    auto queued = [&] { return s_tail < L ? s_tail : L; };
+    // appends the vertices of degree d: lo < d <= hi; returns this thread's minimum degree above hi
+    auto collect = [&](int lo, int hi) {
+        int mn = INT_MAX;
+        for (int v = t; v < L; v += kPeelBlock) {
+            const int d = deg[v];
+            if (d > hi) mn = d < mn ? d : mn;
+            else if (d > lo) push(v);
+        }
+        return mn;
+    };
+    // four neighbours lose one degree each
+    auto update = [&](const ushort4& x) {
+        const int o0 = atomicSub(&deg[x.x], 1), o1 = atomicSub(&deg[x.y], 1);
+        const int o2 = atomicSub(&deg[x.z], 1), o3 = atomicSub(&deg[x.w], 1);
+        if (o0 == c + 1 || o1 == c + 1 || o2 == c + 1 || o3 == c + 1) {
+            if (o0 == c + 1) push(x.x);
+            if (o1 == c + 1) push(x.y);
+            if (o2 == c + 1) push(x.z);
+            if (o3 == c + 1) push(x.w);
+        }
+    };
+    // the frontier that the whole-device rounds left behind (none at a level change)
+    collect(-1, c);
+    __syncthreads();
+    int head = 0, tail = queued();
+    __syncthreads();
+    while (head < L) {
+        if (head == tail) {
+            // the next level is almost always c + 1; otherwise the smallest live degree
+            const int mn = wave_min(collect(c, c + 1));
+            if (lane == 0 && mn != INT_MAX) atomicMin(&s_min, mn);
+            __syncthreads();
+            const bool found = queued() > head;
+            const int next = found ? c + 1 : s_min;
+            __syncthreads();   // the second pass appends: every thread has read the tail by now
+            if (!found) collect(c, next);
+            c = next;
+            __syncthreads();
+            degen = c > degen ? c : degen;
+            tail = queued();
+            __syncthreads();
+            if (t == 0) s_min = INT_MAX;
+            if (tail == head) break;   // cannot happen: a live vertex has the minimum degree
+            r++;
+            continue;
+        }
+        for (int i = head + t; i < tail; i += kPeelBlock) round_of[i] = r;
+        for (int i = head + wave; i < tail; i += NW) {
+            const int2 sp = span[queue[i]];
+            const int b = __builtin_amdgcn_readfirstlane(sp.x);
+            const int e = b + ((__builtin_amdgcn_readfirstlane(sp.y) + 3) & ~3);
+            for (int j0 = b; j0 < e; j0 += 512) {
+                const int j = j0 + 4 * lane;
+                const bool two = j0 + 256 < e;
+                ushort4 x0{}, x1{};
+                if (j < e) x0 = *reinterpret_cast<const ushort4*>(rows + j);
+                if (two && j + 256 < e) x1 = *reinterpret_cast<const ushort4*>(rows + j + 256);
+                if (j < e) update(x0);
+                if (two && j + 256 < e) update(x1);
+            }
+        }
+        __syncthreads();
+        head = tail;
+        tail = queued();
+        r++;
+        __syncthreads();
+    }
+    for (int i = t; i < tail; i += kPeelBlock) key[list[queue[i]]] = round_of[i];
+    if (t == 0) {
         ctl[CTL_DEGEN] = degen;
         ctl[CTL_ROUNDS] = r;
         ctl[CTL_MAXKEY] = r > 0 ? r - 1 : 0;
@@ -756,13 +1021,14 @@ OrientWs carve(void* ws, int n, int nnz, size_t* bytes) {
     w.key_b = c.take<int>(nn);
     w.val_b = c.take<int>(nn);
     w.rank = c.take<int>(nn);
-    w.outdeg = c.take<int>(nn + 1);
     w.tiles = c.take<int>(static_cast<size_t>(ntiles));
-    w.rnd = c.take<int>(nn);
     w.fr0 = c.take<int>(nn);
     w.fr1 = c.take<int>(nn);
     w.hf0 = c.take<int>(nn);
     w.hf1 = c.take<int>(nn);
+    // outdeg, rnd and tmp together hold the peel's compacted rows (nnz + 3 n 16-bit ids)
+    w.outdeg = c.take<int>(nn + 1);
+    w.rnd = c.take<int>(nn);
     w.tmp = c.take<int>(m);
     *bytes = c.bytes();
     return w;
@@ -942,28 +1208,41 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
         KC_CHECK(hipMemcpyAsync(w.ctl + CTL_ROUNDS, &r, sizeof(int), hipMemcpyHostToDevice, s));
         KC_CHECK(hipMemcpyAsync(w.key_a, w.rnd, sizeof(int) * n, hipMemcpyDeviceToDevice, s));
     } else {
-        int occ = 0;
-        KC_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_peel, kBlock, 0));
-        if (occ < 1) return KC_EDEVICE;
-        // Most rounds are small and end in a grid barrier whose cost grows with
-        // the number of blocks: one block per 16k vertices, between 32 and one
-        // per CU (64 blocks peeled the 1M-vertex power-law graph in 37 ms, 256 in 61).
-        int blocks = n / 16384;
-        if (blocks > device_cus()) blocks = device_cus();
-        if (blocks < 32) blocks = 32;
-        if (blocks > occ * device_cus()) blocks = occ * device_cus();   // all blocks co-resident
-        int n_ = n;
-        const int* rp = g->row_ptr;
-        const int* cl = g->col;
         int* deg = w.key_b;   // scratch until the sort
-        void* args[] = {&n_, &rp, &cl, &deg, &w.rnd, &w.fr0, &w.fr1, &w.hf0, &w.hf1, &w.val_a, &w.ctl};
-        KC_CHECK(hipLaunchCooperativeKernel(reinterpret_cast<void*>(k_peel), dim3(blocks), dim3(kBlock),
-                                            args, 0, s));
-        KC_CHECK(hipMemcpyAsync(w.key_a, w.rnd, sizeof(int) * n, hipMemcpyDeviceToDevice, s));
+        if (n > kCoreCap) {
+            // one block per 16k vertices, between 16 and 64 (a barrier costs 0.8 us at
+            // 16 blocks, 1.3 at 64, 3.7 at 256, whatever the block size)
+            int occ = 0;
+            KC_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_peel, kPeelBlock, 0));
+            if (occ < 1) return KC_EDEVICE;
+            int blocks = n / 16384;
+            if (blocks > 64) blocks = 64;
+            if (blocks < 16) blocks = 16;
+            if (blocks > occ * device_cus()) blocks = occ * device_cus();   // all blocks co-resident
+            int n_ = n, keep = kCoreCap;
+            const int* rp = g->row_ptr;
+            const int* cl = g->col;
+            void* args[] = {&n_, &keep, &rp, &cl, &deg, &w.key_a, &w.fr0, &w.fr1, &w.val_a, &w.ctl};
+            KC_CHECK(hipLaunchCooperativeKernel(reinterpret_cast<void*>(k_peel), dim3(blocks), dim3(kPeelBlock),
+                                                args, 0, s));
+        } else {
+            k_peel_init<<<grid_for_threads(n), kBlock, 0, s>>>(n, g->row_ptr, deg, w.key_a, w.val_a, w.ctl);
+        }
+        unsigned short* rows = reinterpret_cast<unsigned short*>(w.outdeg);   // outdeg, rnd, tmp: nnz + 4 n entries
+        int2* span = reinterpret_cast<int2*>(w.hf0);   // hf0 and hf1 are adjacent: 2 n ints and more
+        k_core_list<<<div_up(n, kPeelBlock), kPeelBlock, 0, s>>>(n, w.key_a, deg, w.rank, w.fr0, span, w.ctl);
+        k_core_rows<<<grid_for_waves(n < kCoreCap ? n : kCoreCap), kBlock, 0, s>>>(
+            g->row_ptr, g->col, w.rank, w.fr0, span, rows, w.ctl);
+        const int lds = kCoreLds;
+        KC_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_core_peel),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        k_core_peel<<<1, kPeelBlock, lds, s>>>(span, rows, w.fr0, w.fr1, w.key_a, w.ctl);
+        KC_CHECK(hipGetLastError());
     }
     int hctl[CTL_WORDS];
     KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
     KC_CHECK(hipStreamSynchronize(s));
+    if (order == KC_ORDER_DEGENERACY && !hctl[CTL_DONE]) return KC_EDEVICE;   // a barrier wait ran out
     int bits = 0;
     while (bits < 31 && (hctl[CTL_MAXKEY] >> bits) != 0) bits++;
 
