@@ -119,18 +119,18 @@ inline int s_cap_for(int d_max) { return ((d_max + 31) / 32) * 32 > kLightCap ? 
 inline int piv_level_words(int maxw) { return 3 * maxw + 4; }
 
 // A wavefront's claims on a launch's roots (0 .. nroots - 1, in list order): chunks
-// of a sixteenth of its even share, at most `cap`.  The first chunk is fixed by the
-// wavefront's index, so a launch with no more chunks than wavefronts takes no
-// atomic at all; later ones come from the queue head, whose atomics are served one
-// after the other (11.6 ns each): with 8192 wavefronts that alone was 95 us of a
-// launch over 2000 roots.  The head is not looked at before it is claimed from:
-// plain loads of the contended line wait in the same queue (batch of 10,000
-// graphs: 37 -> 52 ms with such a look).
+// of two thirds of its even share, at most `cap`.  The first chunk is fixed by the
+// wavefront's index; later ones come from the queue head, whose atomics are served
+// one after the other, 11.6 ns each: one per wavefront was 95 us of a launch over
+// 2000 roots, one per root 2.3 ms of a count over 198,000.  Two thirds leave at most
+// half a claim per wavefront (48 us) where a list is short, and the cap leaves many
+// where it is long.  The head is not looked at before it is claimed from: plain loads
+// of the contended line wait in the same queue (batch of 10,000 graphs: 37 -> 52 ms).
 //
-// SPREAD: the roots of a chunk lie a chunk count apart instead of side by side.
-// Lists end with the dense core's roots, so neighbours are heavy together: chunks
-// of neighbours took the per-vertex counts of a 200k-vertex power-law graph from
-// 5.2 to 23 ms.  Lists of small roots keep neighbours together, whose rows they share.
+// The roots of a chunk lie a chunk count apart.  Lists end with the dense core's
+// roots and batches hold a graph's roots together, so neighbours are heavy together:
+// chunks of neighbours took the per-vertex counts of a 200k-vertex power-law graph
+// from 5.2 to 23 ms and a batch of 665 graphs at k = 7 from 9.5 to 11.5.
 struct RootClaims {
     int next = 0, left = 0;         // claimed, unprocessed roots
     int step = 1;                   // distance between the roots of a chunk
@@ -140,10 +140,9 @@ struct RootClaims {
 // Claims the next chunk (roots c.next, c.next + c.step, ..., c.left of them;
 // wave-uniform); false when no root is left.  `head` is zero at launch; every lane
 // calls this.
-template <bool SPREAD>
 __device__ __forceinline__ bool claim_chunk(RootClaims& c, int* head, int nroots, int wave, int nwaves, int cap) {
-    int size = nroots / (16 * nwaves);
-    size = size < 1 ? 1 : size > cap ? cap : size;
+    const long long share = (2LL * nroots + 3LL * nwaves - 1) / (3LL * nwaves);
+    const int size = share < 1 ? 1 : share > cap ? cap : static_cast<int>(share);
     const int chunks = (nroots + size - 1) / size;
     int q = wave;
     if (c.started) {
@@ -154,21 +153,15 @@ __device__ __forceinline__ bool claim_chunk(RootClaims& c, int* head, int nroots
     }
     c.started = true;
     if (q >= chunks) return false;
-    if (SPREAD) {
-        c.next = q;
-        c.step = chunks;
-        c.left = (nroots - q + chunks - 1) / chunks;
-    } else {
-        c.next = q * size;
-        c.left = c.next + size < nroots ? size : nroots - c.next;
-    }
+    c.next = q;
+    c.step = chunks;
+    c.left = (nroots - q + chunks - 1) / chunks;
     return true;
 }
 
 // The next root of this wavefront (wave-uniform), or -1 when none is left.
-template <bool SPREAD>
 __device__ __forceinline__ int claim_root(RootClaims& c, int* head, int nroots, int wave, int nwaves, int cap) {
-    if (c.left == 0 && !claim_chunk<SPREAD>(c, head, nroots, wave, nwaves, cap)) return -1;
+    if (c.left == 0 && !claim_chunk(c, head, nroots, wave, nwaves, cap)) return -1;
     const int r = c.next;
     c.next += c.step;
     c.left--;
@@ -361,8 +354,9 @@ int list_orient_launch(const kc_dag* d, int k, bool ec, int* list, long long cap
 
 // Capture-safe degree orientation (kc_orient.hip).
 size_t orient_async_workspace(int n, int nnz);
-int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, int key_bits, int* out_row_ptr,
-                        int* out_col, int* out_src, int* out_perm, void* ws, hipStream_t s);
+int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, const int* voff, int ngraphs,
+                        int max_degree, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, void* ws,
+                        hipStream_t s, bool* grouped);
 
 // LDS bytes one lane-walk wavefront needs for a list of `maxw` words per row.
 inline size_t lane_lds_bytes(int maxw, int k, bool ec, bool pair) {

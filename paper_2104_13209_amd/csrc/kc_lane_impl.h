@@ -635,7 +635,7 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
     for (;;) {
         int slot = -1;
         if (!helping) {
-            slot = claim_root<PAIR>(rc, P.head, nroots, blockIdx.x, nwaves, PAIR ? kPairRootChunk : kRootChunk);
+            slot = claim_root(rc, P.head, nroots, blockIdx.x, nwaves, PAIR ? kPairRootChunk : kRootChunk);
             if (slot < 0) {
                 if (PAIR) helping = true;
                 else break;

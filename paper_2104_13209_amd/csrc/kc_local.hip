@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(64) k_local(LocalParams P) {
     unsigned long long todo = 0;                         // bits: roots of the claimed chunk
     for (;;) {
         if (todo == 0ull) {
-            if (!claim_chunk<true>(rc, P.head, P.nroots, blockIdx.x, gridDim.x, 64)) break;
+            if (!claim_chunk(rc, P.head, P.nroots, blockIdx.x, gridDim.x, 64)) break;
             // the size bound of S decides before any extraction: a lane per root
             int bound = -1;
             if (lane < rc.left) {

@@ -11,6 +11,7 @@
 //             histogram, exclusive scan -> row_ptr (the paper's histogram + scan)
 //   compact   gather each kept row, sort it by new id, write col and the COO src
 #include <climits>
+#include <cstring>
 
 #include "kc_internal.h"
 
@@ -24,13 +25,13 @@ constexpr int kRowCap = KC_MAX_DMAX;            // rows sorted in LDS up to this
 
 // Control words in the orientation workspace.
 enum Ctl {
-    CTL_ERR = 0,       // validation error flag
+    CTL_BAD = 0,       // validation: a malformed row or a missing reverse entry
     CTL_MAXKEY = 1,    // largest sort key
     CTL_DMAX = 2,      // max out-degree
     CTL_DEGEN = 3,     // degeneracy (peel)
     CTL_ROUNDS = 4,    // peel rounds
     CTL_LONG = 5,      // a row longer than kRowCap exists
-    CTL_ZEROS = 6,     // zero count of the current radix pass
+    CTL_TOTAL = 6,     // DAG edges
     CTL_SIZE0 = 8,     // peel frontier sizes, ring of 3 (8, 9, 10)
     CTL_MIN = 11,      // peel level minimum
     CTL_LEVEL = 12,    // peel: current level
@@ -42,56 +43,167 @@ enum Ctl {
     CTL_AD_LIVE = 16,  // approximate degeneracy: vertices left
     CTL_AD_SUM = 18,   // approximate degeneracy: their degree sum (u64 over words 18, 19)
     CTL_BAR = 32,      // peel: barrier arrivals, on a cache line of their own
+    CTL_UP = 34,       // validation: entries to longer rows less those to shorter ones (i64 over words 34, 35)
     CTL_WORDS = 64
 };
 
 // ------------------------------------------------------------ validation
 
-// One wave per vertex.  Every index is clamped before use so that the check is
-// memory-safe on any input.
-__global__ void __launch_bounds__(kBlock) k_validate(int n, int nnz, const int* __restrict__ row_ptr,
-                                                    const int* __restrict__ col, int* ctl) {
+// Kernels over rows: a block of 16 wavefronts takes 16 * per rows in runs of `run`
+// consecutive ones (a power of two up to 16 * per).  Short runs spread the hubs, with
+// which vertices ordered by degree or by peeling round end, over the blocks; a batch's
+// graphs, each with its own hubs, stay together (run = 16 * per: their rows and ranks
+// share cache lines, k_fill 4.6 -> 3.3 ms on the batch of 10,000).  Each wavefront loads the bounds of its `per` rows a lane each
+// and walks rows of up to kLongRow entries four at a time, 16 lanes each: an average
+// row has some 32 entries, and a wavefront per row waits on one chain of loads for
+// each.  Longer rows go to a list in LDS that the whole block then shares.
+constexpr int kRowBlock = 1024;
+constexpr int kLongRow = 256;
+constexpr int kMaxPer = 64;
+constexpr int kRowRun = 16;
+
+struct LongRows {
+    int n;
+    int row[16 * kMaxPer];
+};
+
+// The row of this lane, or -1.
+__device__ __forceinline__ int block_row(int n, int per, int run) {
     const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    int bad = 0;
-    for (int v = wave; v < n; v += nwaves) {
-        int b = row_ptr[v], e = row_ptr[v + 1];
-        if (b < 0 || e < b || e > nnz) { bad = 1; continue; }
-        if (v == 0 && b != 0) bad = 1;
-        if (v == n - 1 && e != nnz) bad = 1;
-        for (int j = b + lane; j < e; j += 64) {
-            int w = col[j];
-            if (w < 0 || w >= n || w == v) { bad = 1; continue; }
-            if (j > b && col[j - 1] >= w) bad = 1;
-            int lo = row_ptr[w], hi = row_ptr[w + 1];
-            lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
-            hi = hi < lo ? lo : (hi > nnz ? nnz : hi);
-            while (lo < hi) {
-                int mid = lo + ((hi - lo) >> 1);
-                if (col[mid] < v) lo = mid + 1; else hi = mid;
-            }
-            int ehi = row_ptr[w + 1];
-            ehi = ehi > nnz ? nnz : ehi;
-            if (lo >= ehi || col[lo] != v) bad = 1;
-        }
+    const int k = (threadIdx.x >> 6) * per + lane;
+    const long long i = (static_cast<long long>(k / run) * gridDim.x + blockIdx.x) * run + k % run;
+    return lane < per && i < n ? static_cast<int>(i) : -1;
+}
+
+// step(lane that holds the row's bounds, first entry of the row, entry, in range), called by all
+// lanes together, for this wavefront's short rows.
+template <class Step>
+__device__ __forceinline__ void short_rows(int b, int e, int per, int lane, Step step) {
+    const int shown = e - b > kLongRow ? b : e;
+    for (int q = 0; 4 * q < per; q++) {
+        const int from = 4 * q + (lane >> 4);
+        const int gb = __shfl(b, from), ge = __shfl(shown, from);
+        const int span = wave_max(ge - gb);
+        for (int t = 0; t < span; t += 16) step(from, gb, gb + t + (lane & 15), gb + t + (lane & 15) < ge);
     }
-    if (__ballot(bad) && lane == 0) atomicOr(&ctl[CTL_ERR], 1);
+}
+
+// Sorted, simple, symmetric?  Every index is clamped before use so that the check
+// is memory-safe on any input.  Symmetry: an entry (v, w) points down when w's row
+// is shorter (ties: smaller id).  Every down entry must find v in w's row, the
+// shorter one of the two; rows hold no entry twice, so if also as many entries point
+// up as down, every up entry is the reverse of one of them.  That halves the
+// searches of testing every entry and keeps them out of the hubs' rows: 2,870 us on
+// the 1M-vertex power-law graph before.  Bound by the gathers of the searches.
+__global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per, int run, const int* __restrict__ row_ptr,
+                                                       const int* __restrict__ col, int* ctl) {
+    __shared__ long long s_up;
+    __shared__ int s_bad;
+    __shared__ LongRows longs;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) {
+        s_up = 0;
+        s_bad = 0;
+        longs.n = 0;
+    }
+    __syncthreads();
+    int bad = 0;
+    long long up = 0;                                 // entries that point up, less those that point down
+    const int row = block_row(n, per, run);
+    int b = 0, e = 0;
+    if (row >= 0) {
+        b = row_ptr[row];
+        e = row_ptr[row + 1];
+        if ((row == 0 && b != 0) || (row == n - 1 && e != nnz)) bad = 1;
+        if (b < 0 || e < b || e > nnz) {
+            bad = 1;
+            b = e = 0;
+        }
+        if (e - b > kLongRow) longs.row[atomicAdd(&longs.n, 1)] = row;
+    }
+    auto check = [&](int v, int dv, int first, int j) {
+        const int w = col[j];
+        if (w < 0 || w >= n || w == v) {
+            bad = 1;
+            return;
+        }
+        if (j > first && col[j - 1] >= w) bad = 1;
+        int lo = row_ptr[w], hi = row_ptr[w + 1];
+        lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
+        hi = hi < lo ? lo : (hi > nnz ? nnz : hi);
+        const int dw = hi - lo;
+        if (dw > dv || (dw == dv && w > v)) {
+            up++;
+            return;
+        }
+        up--;
+        const int end = hi;
+        while (lo < hi) {
+            const int mid = lo + ((hi - lo) >> 1);
+            if (col[mid] < v) lo = mid + 1; else hi = mid;
+        }
+        if (lo >= end || col[lo] != v) bad = 1;
+    };
+    short_rows(b, e, per, lane, [&](int from, int first, int j, bool in) {
+        const int v = __shfl(row, from), dv = __shfl(e - b, from);
+        if (in) check(v, dv, first, j);
+    });
+    __syncthreads();
+    for (int l = 0; l < longs.n; l++) {
+        const int v = longs.row[l], first = row_ptr[v], last = row_ptr[v + 1];
+        for (int j = first + threadIdx.x; j < last; j += kRowBlock) check(v, last - first, first, j);
+    }
+    up = wave_sum(up);
+    if (lane == 0 && up) atomicAdd(reinterpret_cast<unsigned long long*>(&s_up), static_cast<unsigned long long>(up));
+    if (bad) s_bad = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_up) atomicAdd(reinterpret_cast<unsigned long long*>(ctl + CTL_UP), static_cast<unsigned long long>(s_up));
+        if (s_bad) atomicOr(&ctl[CTL_BAD], 1);
+    }
+}
+
+// An invalid graph: nothing after the validation may follow its indices.
+__device__ __forceinline__ bool rejected(const int* ctl) {
+    return ctl[CTL_BAD] != 0 || *reinterpret_cast<const long long*>(ctl + CTL_UP) != 0;
 }
 
 // --------------------------------------------------------------- keys
 
-__global__ void __launch_bounds__(kBlock) k_degree_key(int n, const int* __restrict__ row_ptr,
-                                                      int* key, int* val, int* ctl) {
+// Largest value of a block into *out, one atomic per block (an atomic per wavefront
+// on the one address took 181 us of a 1M-vertex degree pass).
+__device__ __forceinline__ void block_max_to(int x, int* sh, int* out) {
+    if (threadIdx.x == 0) *sh = 0;
+    __syncthreads();
+    x = wave_max(x);
+    if ((threadIdx.x & 63) == 0 && x > 0) atomicMax(sh, x);
+    __syncthreads();
+    if (threadIdx.x == 0 && *sh > 0) atomicMax(out, *sh);
+}
+
+// key = degree, or with `voff` (batches) graph * key_span + degree, so that every
+// graph's vertices stay together.
+__global__ void __launch_bounds__(kBlock) k_degree_key(int n, const int* __restrict__ row_ptr, int* key, int* val,
+                                                      int* ctl, const int* __restrict__ voff, int ngraphs,
+                                                      int key_span) {
+    __shared__ int sh;
+    if (rejected(ctl)) return;
     int mx = 0;
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
         int d = row_ptr[v + 1] - row_ptr[v];
+        if (voff) {
+            int lo = 0, hi = ngraphs;                        // voff[lo] <= v < voff[hi]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (voff[mid] <= v) lo = mid; else hi = mid;
+            }
+            d += lo * key_span;
+        }
         key[v] = d;
         val[v] = v;
         mx = d > mx ? d : mx;
     }
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) atomicMax(&ctl[CTL_MAXKEY], mx);
+    block_max_to(mx, &sh, &ctl[CTL_MAXKEY]);
 }
 
 // --------------------------------------------------- degeneracy order (peeling)
@@ -124,6 +236,8 @@ __global__ void __launch_bounds__(kBlock) k_degree_key(int n, const int* __restr
 
 constexpr int kPeelBlock = 1024;
 constexpr int kCoreCap = 26000;   // 6 bytes of LDS each, of 160 KB
+constexpr int kCoreFront = 96;
+constexpr int kCoreSmall = 4000;  // up to here the one workgroup does all rounds
 constexpr int kCoreLds = 6 * kCoreCap + 8;
 constexpr int kPeelSpins = 1 << 22;
 
@@ -207,7 +321,10 @@ __device__ __forceinline__ void peel_row(int j, int first, int e, int stride, in
     }
 }
 
-// The whole-device rounds: until at most `keep` vertices are left.  A frontier of
+// The whole-device rounds: until at most `keep` vertices are left and frontiers are
+// small (kCoreFront vertices on a running average).  Graphs without a skewed core peel
+// in wide fronts to the end, which one compute unit is slow at: G(26000, 20 / n) takes
+// 1,390 us with all of it in one workgroup.  A frontier of
 // f vertices gets the nwaves / f wavefronts (at most 64) that there are for each,
 // so that the hubs' long rows are shared while frontiers are small.  Leaves the
 // level in CTL_LEVEL, the rounds so far in CTL_ROUNDS, the degrees of the vertices
@@ -224,6 +341,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
     const int nwaves = nth >> 6;
     int* bar = ctl + CTL_BAR;
     int epoch = 0;
+    if (rejected(ctl)) return;
 
     for (int v = tid; v < n; v += nth) {
         st_agent(&deg[v], row_ptr[v + 1] - row_ptr[v]);
@@ -238,7 +356,8 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
     if (!peel_barrier(bar, epoch, &ok)) return;
 
     int removed = 0, r = 0, c = -1, degen = 0;
-    while (n - removed > keep) {
+    int recent = n;                                  // goes to 32 times the frontier size of late
+    while (n - removed > keep || (recent > 32 * kCoreFront && removed < n)) {
         const int* cur = (r & 1) ? fr1 : fr0;
         const PeelNext nx{(r & 1) ? fr0 : fr1, &ctl[CTL_SIZE0 + (r + 1) % 3], buf, &count};
         const int fsize = ld_acquire(&ctl[CTL_SIZE0 + r % 3]);
@@ -323,6 +442,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
         }
         peel_flush(nx, &base);
         removed += fsize;
+        recent += fsize - recent / 32;
         r++;
         if (!peel_barrier(bar, epoch, &ok)) return;
     }
@@ -335,9 +455,10 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
     }
 }
 
-// Graphs of at most kCoreCap vertices start in the one-workgroup peel.
+// Graphs of at most kCoreSmall vertices start in the one-workgroup peel.
 __global__ void __launch_bounds__(kBlock) k_peel_init(int n, const int* __restrict__ row_ptr, int* deg, int* key,
                                                      int* val, int* ctl) {
+    if (rejected(ctl)) return;
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
         deg[v] = row_ptr[v + 1] - row_ptr[v];
         key[v] = -1;
@@ -358,6 +479,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_list(int n, const int* __re
                                                          int* ctl) {
     __shared__ int cnt[kPeelBlock / 64], sum[kPeelBlock / 64];
     __shared__ int base_id, base_at;
+    if (rejected(ctl)) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int v = blockIdx.x * kPeelBlock + threadIdx.x;
     const bool live = v < n && key[v] < 0;
@@ -790,24 +912,68 @@ __global__ void __launch_bounds__(kBlock) k_cl_round(int r, ClFront f, const int
     if (lane == 0 && mx > 0) atomicMax(&ctl[CTL_MAXKEY], mx);
 }
 
-__global__ void __launch_bounds__(kBlock) k_tile_sum(int count, const int* __restrict__ in, int bit,
-                                                    int mode, int* tile_sum) {
-    __shared__ int sh[kBlock / 64 + 1];
+// Exclusive scan of a non-negative array, out[count] = total, and its maximum into
+// *top; arrays of up to kScanOne entries by one block, others in three passes.
+constexpr int kScanOne = 8192;
+
+__global__ void __launch_bounds__(1024) k_scan_one(int count, const int* __restrict__ in, int* out, int* top,
+                                                  int* ctl) {
+    __shared__ int sums[16], s_top;
+    if (rejected(ctl)) return;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int per = (count + 1023) / 1024, b = threadIdx.x * per;
+    int v[kScanOne / 1024];
+    int s = 0, mx = 0;
+#pragma unroll
+    for (int i = 0; i < kScanOne / 1024; i++) {
+        v[i] = i < per && b + i < count ? in[b + i] : 0;
+        s += v[i];
+        mx = v[i] > mx ? v[i] : mx;
+    }
+    int inc = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += y;
+    }
+    if (lane == 63) sums[w] = inc;
+    block_max_to(mx, &s_top, top);
+    int run = inc - s;
+    for (int i = 0; i < w; i++) run += sums[i];
+#pragma unroll
+    for (int i = 0; i < kScanOne / 1024; i++) {
+        if (i < per && b + i < count) out[b + i] = run;
+        run += v[i];
+    }
+    if (threadIdx.x == 1023) {
+        out[count] = run;
+        ctl[CTL_TOTAL] = run;
+    }
+}
+
+// Pass 1: per-tile sums, and the maximum.
+__global__ void __launch_bounds__(kBlock) k_tile_sum(int count, const int* __restrict__ in, int* tile_sum, int* top,
+                                                    const int* ctl) {
+    __shared__ int sh[kBlock / 64 + 1], s_top;
+    if (rejected(ctl)) return;
     const int base = blockIdx.x * kTile + threadIdx.x * kItems;
-    int s = 0;
+    int s = 0, mx = 0;
 #pragma unroll
     for (int i = 0; i < kItems; i++) {
-        int idx = base + i;
-        if (idx < count) s += mode == 0 ? in[idx] : (((in[idx] >> bit) & 1) == 0);
+        const int x = base + i < count ? in[base + i] : 0;
+        s += x;
+        mx = x > mx ? x : mx;
     }
     int tot;
     block_exclusive_scan(s, &tot, sh);
     if (threadIdx.x == 0) tile_sum[blockIdx.x] = tot;
+    block_max_to(mx, &s_top, top);
 }
 
-// Pass 2: exclusive scan of the tile sums by one block; total into *total.
-__global__ void __launch_bounds__(kBlock) k_scan_tiles(int ntiles, int* tile_sum, int* total) {
+// Pass 2: exclusive scan of the tile sums by one block; the total to CTL_TOTAL.
+__global__ void __launch_bounds__(kBlock) k_scan_tiles(int ntiles, int* tile_sum, int* ctl) {
     __shared__ int sh[kBlock / 64 + 1];
+    if (rejected(ctl)) return;
     int carry = 0;
     for (int base = 0; base < ntiles; base += kBlock) {
         int idx = base + threadIdx.x;
@@ -817,15 +983,14 @@ __global__ void __launch_bounds__(kBlock) k_scan_tiles(int ntiles, int* tile_sum
         if (idx < ntiles) tile_sum[idx] = ex + carry;
         carry += tot;
     }
-    if (threadIdx.x == 0) *total = carry;
+    if (threadIdx.x == 0) ctl[CTL_TOTAL] = carry;
 }
 
-// Pass 3 (mode 0): out[i] = exclusive prefix of in[] (+ tile offset); out[count]
-// = total.
+// Pass 3: out[i] = exclusive prefix of in[]; out[count] = total.
 __global__ void __launch_bounds__(kBlock) k_scan_apply(int count, const int* __restrict__ in,
-                                                      const int* __restrict__ tile_off,
-                                                      const int* __restrict__ total, int* out) {
+                                                      const int* __restrict__ tile_off, int* out, const int* ctl) {
     __shared__ int sh[kBlock / 64 + 1];
+    if (rejected(ctl)) return;
     const int base = blockIdx.x * kTile + threadIdx.x * kItems;
     int v[kItems];
     int s = 0;
@@ -843,113 +1008,301 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(int count, const int* __r
         if (idx < count) out[idx] = run;
         run += v[i];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = *total;
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[count] = ctl[CTL_TOTAL];
 }
 
-// Pass 3 (radix): stable split on `bit`: zeros keep their order at the front,
-// ones keep their order after all zeros.
-__global__ void __launch_bounds__(kBlock) k_radix_scatter(int count, int bit, const int* __restrict__ kin,
-                                                         const int* __restrict__ vin,
-                                                         const int* __restrict__ tile_off,
-                                                         const int* __restrict__ zeros, int* kout,
-                                                         int* vout) {
-    __shared__ int sh[kBlock / 64 + 1];
-    const int base = blockIdx.x * kTile + threadIdx.x * kItems;
-    int k[kItems];
-    int s = 0;
+// Stable LSD radix sort of (key, id), eight bits a pass over tiles of 2048 entries:
+// per-tile digit counts, a scan of each digit's counts over the tiles, and a
+// scatter in which every wavefront ranks 512 consecutive entries by matching
+// digits with eight ballots.  A pass whose digit is zero in every key (they are known
+// on the device only) does nothing, so the sorted data is in buffer A after an even
+// number of working passes and in B after an odd one (radix_passes).  One bit a pass,
+// as before, took 36 launches and 240 us for 1M vertices of degree < 2^12, and 24
+// launches and 70 us for 2,000 vertices.
+__device__ __forceinline__ int radix_passes(const int* ctl) {
+    const unsigned int mk = static_cast<unsigned int>(ctl[CTL_MAXKEY]);
+    return mk == 0u ? 0 : (39 - __clz(static_cast<int>(mk))) >> 3;
+}
+
+struct RadixBuf {
+    int *key_a, *val_a, *key_b, *val_b;
+};
+
+__global__ void __launch_bounds__(kBlock) k_radix_hist(int count, int pass, RadixBuf rb, int* hist, const int* ctl) {
+    __shared__ int cnt[256];
+    if (rejected(ctl) || pass >= radix_passes(ctl)) return;
+    const int* key = (pass & 1) ? rb.key_b : rb.key_a;
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int base = blockIdx.x * kTile;
 #pragma unroll
     for (int i = 0; i < kItems; i++) {
-        int idx = base + i;
-        k[i] = idx < count ? kin[idx] : 0;
-        s += idx < count ? (((k[i] >> bit) & 1) == 0) : 0;
+        const int idx = base + i * kBlock + threadIdx.x;
+        if (idx < count) atomicAdd(&cnt[(static_cast<unsigned int>(key[idx]) >> (8 * pass)) & 255u], 1);
     }
-    int tot;
-    int zb = block_exclusive_scan(s, &tot, sh) + tile_off[blockIdx.x];
-    const int nz = *zeros;
+    __syncthreads();
+    hist[threadIdx.x * gridDim.x + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// Block d: exclusive scan of digit d's counts over the tiles; its total to dtot[d].
+__global__ void __launch_bounds__(kBlock) k_radix_scan(int ntiles, int pass, int* hist, int* dtot, const int* ctl) {
+    __shared__ int sh[kBlock / 64 + 1];
+    if (rejected(ctl) || pass >= radix_passes(ctl)) return;
+    int* h = hist + blockIdx.x * ntiles;
+    int carry = 0;
+    for (int base = 0; base < ntiles; base += kBlock) {
+        const int idx = base + threadIdx.x;
+        const int x = idx < ntiles ? h[idx] : 0;
+        int tot;
+        const int ex = block_exclusive_scan(x, &tot, sh);
+        if (idx < ntiles) h[idx] = ex + carry;
+        carry += tot;
+    }
+    if (threadIdx.x == 0) dtot[blockIdx.x] = carry;
+}
+
+__global__ void __launch_bounds__(kBlock) k_radix_scatter(int count, int pass, RadixBuf rb, const int* __restrict__ hist,
+                                                         const int* __restrict__ dtot, const int* ctl) {
+    constexpr int NW = kBlock / 64;
+    __shared__ int sh[NW + 1];
+    __shared__ int at[NW][256];
+    if (rejected(ctl) || pass >= radix_passes(ctl)) return;
+    const int* kin = (pass & 1) ? rb.key_b : rb.key_a;
+    const int* vin = (pass & 1) ? rb.val_b : rb.val_a;
+    int* kout = (pass & 1) ? rb.key_a : rb.key_b;
+    int* vout = (pass & 1) ? rb.val_a : rb.val_b;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < NW * 256; i += kBlock) at[i >> 8][i & 255] = 0;
+    __syncthreads();
+    const int base = blockIdx.x * kTile + w * (kTile / NW);
+    int key[kItems], rank[kItems];
 #pragma unroll
     for (int i = 0; i < kItems; i++) {
-        int idx = base + i;
+        const int idx = base + i * 64 + lane;
+        key[i] = idx < count ? kin[idx] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const bool in = base + i * 64 + lane < count;
+        const unsigned int d = (static_cast<unsigned int>(key[i]) >> (8 * pass)) & 255u;
+        unsigned long long same = __ballot(in);
+#pragma unroll
+        for (int bit = 0; bit < 8; bit++) {
+            const unsigned long long m = __ballot((d >> bit) & 1u);
+            same &= ((d >> bit) & 1u) ? m : ~m;
+        }
+        const int before = __popcll(same & lanemask_lt());
+        const int seen = at[w][d];
+        rank[i] = seen + before;
+        wave_sync_lds();
+        if (in && before == 0) at[w][d] = seen + __popcll(same);
+        wave_sync_lds();
+    }
+    __syncthreads();
+    // digit threadIdx.x: where this tile's entries of it start, wavefront by wavefront
+    int tot;
+    int run = block_exclusive_scan(dtot[threadIdx.x], &tot, sh) + hist[threadIdx.x * gridDim.x + blockIdx.x];
+#pragma unroll
+    for (int i = 0; i < NW; i++) {
+        const int x = at[i][threadIdx.x];
+        at[i][threadIdx.x] = run;
+        run += x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const int idx = base + i * 64 + lane;
         if (idx < count) {
-            int one = (k[i] >> bit) & 1;
-            int pos = one ? nz + (idx - zb) : zb;
-            kout[pos] = k[i];
+            const int pos = at[w][(static_cast<unsigned int>(key[i]) >> (8 * pass)) & 255u] + rank[i];
+            kout[pos] = key[i];
             vout[pos] = vin[idx];
-            zb += one ? 0 : 1;
         }
     }
 }
 
 // --------------------------------------------------------- filter, compact
 
-__global__ void __launch_bounds__(kBlock) k_rank(int n, const int* __restrict__ perm, int* rank) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        rank[perm[i]] = i;
+// perm = the sorted ids, rank = its inverse.
+__global__ void __launch_bounds__(kBlock) k_rank(int n, RadixBuf rb, int* perm, int* rank, const int* ctl) {
+    if (rejected(ctl)) return;
+    const int* val = (radix_passes(ctl) & 1) ? rb.val_b : rb.val_a;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const int v = val[i];
+        perm[i] = v;
+        rank[v] = i;
+    }
 }
 
 // Out-degree of new vertex i: neighbours of perm[i] with a larger new id.
-__global__ void __launch_bounds__(kBlock) k_outdeg(int n, const int* __restrict__ row_ptr,
-                                                  const int* __restrict__ col, const int* __restrict__ perm,
-                                                  const int* __restrict__ rank, int* outdeg, int* ctl) {
+__global__ void __launch_bounds__(kRowBlock) k_outdeg(int n, int per, int run, const int* __restrict__ row_ptr,
+                                                     const int* __restrict__ col, const int* __restrict__ perm,
+                                                     const int* __restrict__ rank, int* outdeg, const int* ctl) {
+    __shared__ int cnt_all[kRowBlock / 64][64];
+    __shared__ LongRows longs;
+    if (rejected(ctl)) return;
     const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    int mx = 0;
-    for (int i = wave; i < n; i += nwaves) {
-        int v = perm[i];
-        int b = row_ptr[v], e = row_ptr[v + 1];
-        int cnt = 0;
-        for (int j = b + lane; j < e; j += 64) cnt += rank[col[j]] > i;
-        cnt = wave_sum(cnt);
-        if (lane == 0) outdeg[i] = cnt;
-        mx = cnt > mx ? cnt : mx;
+    int* cnt = cnt_all[threadIdx.x >> 6];
+    if (threadIdx.x == 0) longs.n = 0;
+    __syncthreads();
+    const int i = block_row(n, per, run);
+    int b = 0, e = 0;
+    if (i >= 0) {
+        const int v = perm[i];
+        b = row_ptr[v];
+        e = row_ptr[v + 1];
+        if (e - b > kLongRow) longs.row[atomicAdd(&longs.n, 1)] = i;
     }
-    if (lane == 0) atomicMax(&ctl[CTL_DMAX], mx);
+    const int len = e - b > kLongRow ? 0 : e - b;
+    for (int q = 0; 4 * q < per; q++) {
+        const int from = 4 * q + (lane >> 4);
+        const int gb = __shfl(b, from) + (lane & 15), row = __shfl(i, from), span = wave_max(__shfl(len, from));
+        const int ge = gb - (lane & 15) + __shfl(len, from);
+        int c = 0;
+        for (int t = 0; t < span; t += 64) {
+            int r[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = gb + t + 16 * u < ge ? col[gb + t + 16 * u] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = r[u] >= 0 ? rank[r[u]] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) c += r[u] > row;
+        }
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
+        if ((lane & 15) == 0) cnt[from] = c;
+    }
+    wave_sync_lds();
+    if (i >= 0 && e - b <= kLongRow) outdeg[i] = cnt[lane];
+    __syncthreads();
+    for (int l = 0; l < longs.n; l++) {
+        const int row = longs.row[l], v = perm[row];
+        const int last = row_ptr[v + 1];
+        if (threadIdx.x == 0) cnt_all[0][0] = 0;
+        __syncthreads();
+        int c = 0;
+        for (int j = row_ptr[v] + threadIdx.x; j < last; j += kRowBlock) c += rank[col[j]] > row;
+        c = wave_sum(c);
+        if (lane == 0 && c) atomicAdd(&cnt_all[0][0], c);
+        __syncthreads();
+        if (threadIdx.x == 0) outdeg[row] = cnt_all[0][0];
+        __syncthreads();
+    }
 }
 
-// Gather row i's kept neighbours (as new ids) into LDS, then place each at its
-// rank within the row (count of smaller entries): col[] rows come out sorted.
-// Rows longer than kRowCap go to tmp[] unsorted and are finished by
-// k_sort_long_rows.
-__global__ void __launch_bounds__(kBlock) k_fill(int n, const int* __restrict__ row_ptr,
-                                                const int* __restrict__ col, const int* __restrict__ perm,
-                                                const int* __restrict__ rank,
-                                                const int* __restrict__ dag_ptr, int* dag_col, int* dag_src,
-                                                int* tmp, int* ctl) {
-    __shared__ int rows[kBlock / 64][kRowCap];
+// Gathers row i's kept neighbours (as new ids) into LDS, then places each at its
+// rank within the row (count of smaller entries): col[] rows come out sorted.  Rows
+// of up to kLongRow neighbours of which at most kGroupRow are kept are handled by 16
+// lanes, the others by the whole block.  Rows of more than kRowCap kept neighbours
+// go to tmp[] unsorted and are finished by k_sort_long_rows.  Bound by the gathers of ranks.
+constexpr int kGroupRow = 64;
+
+__global__ void __launch_bounds__(kRowBlock) k_fill(int n, int per, int run, const int* __restrict__ row_ptr,
+                                                   const int* __restrict__ col, const int* __restrict__ perm,
+                                                   const int* __restrict__ rank,
+                                                   const int* __restrict__ dag_ptr, int* dag_col, int* dag_src,
+                                                   int* tmp, int* ctl) {
+    // a group's rows lie 16 words further apart than they are long, so that the four
+    // broadcasts of a step use different banks
+    __shared__ __align__(16) int groups[kRowBlock / 16][kGroupRow + 16];
+    __shared__ __align__(16) int big_row[kRowCap + 4];
+    __shared__ LongRows longs;
+    __shared__ int s_pos;
+    if (rejected(ctl)) return;
     const int lane = threadIdx.x & 63;
-    const int wslot = threadIdx.x >> 6;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    int* row = rows[wslot];
-    for (int i = wave; i < n; i += nwaves) {
-        const int base = dag_ptr[i];
-        const int len = dag_ptr[i + 1] - base;
-        if (len == 0) continue;
-        const bool in_lds = len <= kRowCap;
-        int* dst = in_lds ? row : tmp + base;
-        int v = perm[i];
-        int b = row_ptr[v], e = row_ptr[v + 1];
-        int pos = 0;
-        for (int j0 = b; j0 < e; j0 += 64) {
-            int j = j0 + lane;
-            int r = j < e ? rank[col[j]] : -1;
-            bool keep = r > i;
-            unsigned long long mask = __ballot(keep);
-            if (keep) dst[pos + __popcll(mask & lanemask_lt())] = r;
-            pos += __popcll(mask);
-        }
-        if (in_lds) {
-            wave_sync_lds();
-            for (int t = lane; t < len; t += 64) {
-                int x = row[t];
-                int below = 0;
-                for (int q = 0; q < len; q++) below += row[q] < x;
-                dag_col[base + below] = x;
-                dag_src[base + below] = i;
+    const int g = lane >> 4, gl = lane & 15;
+    int* grow = groups[threadIdx.x >> 4];
+    const unsigned int glt = (1u << gl) - 1u;
+    if (threadIdx.x == 0) longs.n = 0;
+    __syncthreads();
+    const int row = block_row(n, per, run);
+    int at = 0, len = 0, b = 0, e = 0;
+    if (row >= 0) {
+        at = dag_ptr[row];
+        len = dag_ptr[row + 1] - at;
+        if (len > 0) {
+            const int v = perm[row];
+            b = row_ptr[v];
+            e = row_ptr[v + 1];
+            if (e - b > kLongRow || len > kGroupRow) {
+                longs.row[atomicAdd(&longs.n, 1)] = row;
+                len = 0;
             }
-            wave_sync_lds();
-        } else if (lane == 0) {
-            atomicOr(&ctl[CTL_LONG], 1);
+        }
+    }
+    for (int q = 0; 4 * q < per; q++) {
+        const int from = 4 * q + g;
+        const int rlen = __shfl(len, from);
+        if (__ballot(rlen > 0) == 0ull) continue;
+        const int rat = __shfl(at, from), rb = __shfl(b, from), rend = __shfl(e, from), i = __shfl(row, from);
+        const int re = rlen > 0 ? rend : rb;
+        const int span = wave_max(re - rb);
+        int pos = 0;
+        for (int t = 0; t < span; t += 64) {
+            int r[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = rb + t + 16 * u + gl < re ? col[rb + t + 16 * u + gl] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = r[u] >= 0 ? rank[r[u]] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const unsigned int m = static_cast<unsigned int>(__ballot(r[u] > i) >> (16 * g)) & 0xffffu;
+                if (r[u] > i) grow[pos + __popc(m & glt)] = r[u];
+                pos += __popc(m);
+            }
+        }
+        if (gl < 4) grow[pos + gl] = INT_MAX;        // fills the last four
+        wave_sync_lds();
+        const int longest = wave_max(rlen);
+        for (int t = 0; t < longest; t += 16) {
+            const int x = t + gl < rlen ? grow[t + gl] : INT_MAX;
+            int below = 0;
+            for (int u = 0; u < rlen; u += 4) {
+                const int4 y = *reinterpret_cast<const int4*>(grow + u);
+                below += (y.x < x) + (y.y < x) + (y.z < x) + (y.w < x);
+            }
+            if (t + gl < rlen) {
+                dag_col[rat + below] = x;
+                dag_src[rat + t + gl] = i;
+            }
+        }
+        wave_sync_lds();
+    }
+    __syncthreads();
+    for (int l = 0; l < longs.n; l++) {
+        const int i = longs.row[l], v = perm[i];
+        const int base = dag_ptr[i], rlen = dag_ptr[i + 1] - base;
+        const int last = row_ptr[v + 1];
+        const bool in_lds = rlen <= kRowCap;
+        int* dst = in_lds ? big_row : tmp + base;
+        if (threadIdx.x == 0) {
+            s_pos = 0;
+            if (!in_lds) atomicOr(&ctl[CTL_LONG], 1);
+        }
+        __syncthreads();
+        for (int j0 = row_ptr[v]; j0 < last; j0 += kRowBlock) {
+            const int j = j0 + threadIdx.x;
+            const int r = j < last ? rank[col[j]] : -1;
+            const unsigned long long m = __ballot(r > i);
+            int p = 0;
+            if (lane == 0 && m) p = atomicAdd(&s_pos, __popcll(m));
+            p = __shfl(p, 0) + __popcll(m & lanemask_lt());
+            if (r > i && p < rlen) dst[p] = r;      // any order: the row is sorted afterwards
+        }
+        __syncthreads();
+        if (in_lds) {
+            if (threadIdx.x < 4) big_row[rlen + threadIdx.x] = INT_MAX;   // fills the last four
+            __syncthreads();
+            if (static_cast<int>(threadIdx.x) < rlen) {
+                const int x = big_row[threadIdx.x];
+                int below = 0;
+                for (int u = 0; u < rlen; u += 4) {
+                    const int4 y = *reinterpret_cast<const int4*>(big_row + u);
+                    below += (y.x < x) + (y.y < x) + (y.z < x) + (y.w < x);
+                }
+                dag_col[base + below] = x;
+                dag_src[base + threadIdx.x] = i;
+            }
+            __syncthreads();
         }
     }
 }
@@ -961,8 +1314,9 @@ constexpr int kLongSortCap = 8192;
 
 __global__ void __launch_bounds__(kBlock) k_sort_long_rows(int n, const int* __restrict__ dag_ptr,
                                                           const int* __restrict__ tmp, int* dag_col,
-                                                          int* dag_src) {
+                                                          int* dag_src, const int* ctl) {
     __shared__ int buf[kLongSortCap];
+    if (rejected(ctl) || !ctl[CTL_LONG]) return;
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const int base = dag_ptr[i];
         const int len = dag_ptr[i + 1] - base;
@@ -1020,8 +1374,11 @@ OrientWs carve(void* ws, int n, int nnz, size_t* bytes) {
     w.val_a = c.take<int>(nn);
     w.key_b = c.take<int>(nn);
     w.val_b = c.take<int>(nn);
-    w.rank = c.take<int>(nn);
+    // from tiles on, everything is idle during the radix sort, whose digit counts
+    // (256 per tile of 2048 vertices, and 256 totals) start there: 512 ints for the
+    // smallest graphs (eight slices of 64), 0.13 n + 256 of 7 n for large ones
     w.tiles = c.take<int>(static_cast<size_t>(ntiles));
+    w.rank = c.take<int>(nn);
     w.fr0 = c.take<int>(nn);
     w.fr1 = c.take<int>(nn);
     w.hf0 = c.take<int>(nn);
@@ -1041,6 +1398,15 @@ int grid_for_waves(long long items_per_wave_units) {
     return static_cast<int>(blocks < 1 ? 1 : blocks);
 }
 
+// Rows per wavefront of the row kernels: about four blocks per CU, 4 (one per group
+// of 16 lanes) to 64 rows, a power of two.
+int rows_per_wave(int n) {
+    const int per = n / (16 * 4 * device_cus());
+    int p = 4;
+    while (p < kMaxPer && 2 * p <= per) p *= 2;
+    return p;
+}
+
 int grid_for_threads(long long n) {
     long long blocks = (n + kBlock - 1) / kBlock;
     long long cap = static_cast<long long>(device_cus()) * 16;
@@ -1048,23 +1414,57 @@ int grid_for_threads(long long n) {
     return static_cast<int>(blocks < 1 ? 1 : blocks);
 }
 
-// out[0..count] = exclusive prefix sums of in[0..count) with out[count] = total.
-int exclusive_scan(int count, const int* in, int* out, int* tiles, int* total, hipStream_t s) {
-    int ntiles = div_up(count, kTile);
-    if (ntiles < 1) ntiles = 1;
-    k_tile_sum<<<ntiles, kBlock, 0, s>>>(count, in, 0, 0, tiles);
-    k_scan_tiles<<<1, kBlock, 0, s>>>(ntiles, tiles, total);
-    k_scan_apply<<<ntiles, kBlock, 0, s>>>(count, in, tiles, total, out);
+// One atomic per block on the largest key: at most two blocks per CU.
+int grid_for_keys(long long n) {
+    const int g = grid_for_threads(n), cap = device_cus() * 2;
+    return g < cap ? g : cap;
+}
+
+// out[0..count] = exclusive prefix sums of in[0..count) with out[count] = total (also
+// in CTL_TOTAL); the largest entry to CTL_DMAX.
+int exclusive_scan(int count, const int* in, int* out, int* tiles, int* ctl, hipStream_t s) {
+    if (count <= kScanOne) {
+        k_scan_one<<<1, 1024, 0, s>>>(count, in, out, ctl + CTL_DMAX, ctl);
+    } else {
+        const int ntiles = div_up(count, kTile);
+        k_tile_sum<<<ntiles, kBlock, 0, s>>>(count, in, tiles, ctl + CTL_DMAX, ctl);
+        k_scan_tiles<<<1, kBlock, 0, s>>>(ntiles, tiles, ctl);
+        k_scan_apply<<<ntiles, kBlock, 0, s>>>(count, in, tiles, out, ctl);
+    }
     KC_CHECK(hipGetLastError());
+    return KC_OK;
+}
+
+// Sort by key (key_a / val_a hold the keys and ids, CTL_MAXKEY the largest key, which
+// is at most `bound`), then out: perm, rank, and the DAG's rows.  Nothing is read on
+// the host.
+int build_dag(const OrientWs& w, int n, int nnz, const int* row_ptr, const int* col, long long bound, bool grouped,
+              int* out_row_ptr, int* out_col, int* out_src, int* out_perm, hipStream_t s) {
+    const int ntiles = div_up(n, kTile);
+    const RadixBuf rb{w.key_a, w.val_a, w.key_b, w.val_b};
+    const int per = rows_per_wave(n), rows_grid = div_up(n, 16 * per);
+    const int run = grouped ? 16 * per : kRowRun;
+    int *dtot = w.tiles, *hist = w.tiles + 256;
+    for (int pass = 0; pass < 4 && (bound >> (8 * pass)) != 0; pass++) {
+        k_radix_hist<<<ntiles, kBlock, 0, s>>>(n, pass, rb, hist, w.ctl);
+        k_radix_scan<<<256, kBlock, 0, s>>>(ntiles, pass, hist, dtot, w.ctl);
+        k_radix_scatter<<<ntiles, kBlock, 0, s>>>(n, pass, rb, hist, dtot, w.ctl);
+    }
+    k_rank<<<grid_for_threads(n), kBlock, 0, s>>>(n, rb, out_perm, w.rank, w.ctl);
+    k_outdeg<<<rows_grid, kRowBlock, 0, s>>>(n, per, run, row_ptr, col, out_perm, w.rank, w.outdeg, w.ctl);
+    KC_CHECK(hipGetLastError());
+    const int st = exclusive_scan(n, w.outdeg, out_row_ptr, w.tiles, w.ctl, s);
+    if (st != KC_OK) return st;
+    if (nnz > 0) {
+        k_fill<<<rows_grid, kRowBlock, 0, s>>>(n, per, run, row_ptr, col, out_perm, w.rank, out_row_ptr, out_col, out_src,
+                                              w.tmp, w.ctl);
+        KC_CHECK(hipGetLastError());
+    }
     return KC_OK;
 }
 
 __global__ void __launch_bounds__(kBlock) k_zero(int* p, int count) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) p[i] = 0;
-}
-
-__global__ void __launch_bounds__(kBlock) k_copy(int* dst, const int* src, int count) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) dst[i] = src[i];
 }
 
 }  // namespace
@@ -1075,36 +1475,28 @@ size_t orient_async_workspace(int n, int nnz) {
     return bytes;
 }
 
-// Degree-order orientation with no host synchronisation (every launch size is
-// known on the host: `key_bits` bounds the bit length of the largest degree), so
-// it can be captured in a HIP graph.  Writes row_ptr, col, src, perm; the max
-// out-degree stays on the device (ws control word), unread.
-int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, int key_bits, int* out_row_ptr,
-                        int* out_col, int* out_src, int* out_perm, void* ws, hipStream_t s) {
+// Degree-order orientation of a batch's disjoint union with no host synchronisation,
+// so it can be captured in a HIP graph.  The vertices of a graph stay together (their
+// rows, ranks and roots share cache lines), ordered by (degree, id) inside it, unless
+// graph and degree do not fit one 31-bit key: then the union is ordered by degree.
+// Writes row_ptr, col, src, perm; returns through *grouped whether graphs stay together.
+int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, const int* voff, int ngraphs,
+                        int max_degree, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, void* ws,
+                        hipStream_t s, bool* grouped) {
     size_t need = 0;
     OrientWs w = carve(ws, n, nnz, &need);
     if (n <= 0) return KC_EINVAL;
+    const long long span = static_cast<long long>(max_degree) + 1;
+    const long long keys = span * ngraphs;
+    *grouped = keys <= INT_MAX;
     k_zero<<<1, kBlock, 0, s>>>(w.ctl, CTL_WORDS);
-    k_degree_key<<<grid_for_threads(n), kBlock, 0, s>>>(n, row_ptr, w.key_a, w.val_a, w.ctl);
-    const int ntiles = div_up(n, kTile);
-    int *kin = w.key_a, *vin = w.val_a, *kout = w.key_b, *vout = w.val_b;
-    for (int bit = 0; bit < key_bits; bit++) {
-        k_tile_sum<<<ntiles, kBlock, 0, s>>>(n, kin, bit, 1, w.tiles);
-        k_scan_tiles<<<1, kBlock, 0, s>>>(ntiles, w.tiles, w.ctl + CTL_ZEROS);
-        k_radix_scatter<<<ntiles, kBlock, 0, s>>>(n, bit, kin, vin, w.tiles, w.ctl + CTL_ZEROS, kout, vout);
-        int* t = kin; kin = kout; kout = t;
-        t = vin; vin = vout; vout = t;
-    }
-    k_copy<<<grid_for_threads(n), kBlock, 0, s>>>(out_perm, vin, n);
-    k_rank<<<grid_for_threads(n), kBlock, 0, s>>>(n, out_perm, w.rank);
-    k_outdeg<<<grid_for_waves(n), kBlock, 0, s>>>(n, row_ptr, col, out_perm, w.rank, w.outdeg, w.ctl);
-    KC_CHECK(hipGetLastError());
-    int st = exclusive_scan(n, w.outdeg, out_row_ptr, w.tiles, w.ctl + CTL_ZEROS, s);
+    k_degree_key<<<grid_for_keys(n), kBlock, 0, s>>>(n, row_ptr, w.key_a, w.val_a, w.ctl, *grouped ? voff : nullptr,
+                                                    ngraphs, static_cast<int>(span));
+    int st = build_dag(w, n, nnz, row_ptr, col, *grouped ? keys - 1 : span - 1, *grouped, out_row_ptr, out_col,
+                       out_src, out_perm, s);
     if (st != KC_OK) return st;
     if (nnz > 0) {
-        k_fill<<<grid_for_waves(n), kBlock, 0, s>>>(n, row_ptr, col, out_perm, w.rank, out_row_ptr, out_col,
-                                                   out_src, w.tmp, w.ctl);
-        k_sort_long_rows<<<grid_for_threads(n), kBlock, 0, s>>>(n, out_row_ptr, w.tmp, out_col, out_src);
+        k_sort_long_rows<<<grid_for_threads(n), kBlock, 0, s>>>(n, out_row_ptr, w.tmp, out_col, out_src, w.ctl);
         KC_CHECK(hipGetLastError());
     }
     return KC_OK;
@@ -1121,6 +1513,14 @@ extern "C" KC_API size_t kc_orient_workspace(int32_t n, int32_t nnz, int32_t ord
     carve(nullptr, n, nnz, &bytes);
     return bytes;
 }
+
+namespace {
+bool invalid(const int* hctl) {
+    long long up = 0;
+    std::memcpy(&up, hctl + CTL_UP, sizeof(up));
+    return hctl[CTL_BAD] != 0 || up != 0;
+}
+}  // namespace
 
 extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out, void* ws,
                                     size_t ws_bytes, int32_t validate, void* stream) {
@@ -1151,18 +1551,23 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
         return KC_OK;
     }
 
+    // Rejected graphs stop every later kernel on the device; the orders that read back
+    // on the way look at the verdict first.
     if (validate) {
-        k_validate<<<grid_for_waves(n), kBlock, 0, s>>>(n, nnz, g->row_ptr, g->col, w.ctl);
+        const int per = rows_per_wave(n);
+        k_validate<<<div_up(n, 16 * per), kRowBlock, 0, s>>>(n, nnz, per, kRowRun, g->row_ptr, g->col, w.ctl);
         KC_CHECK(hipGetLastError());
-        int err = 0;
-        KC_CHECK(hipMemcpyAsync(&err, w.ctl + CTL_ERR, sizeof(int), hipMemcpyDeviceToHost, s));
+    }
+    int hctl[CTL_WORDS];
+    if (validate && (order == KC_ORDER_COLOR || order == KC_ORDER_APPROX_DEGENERACY)) {
+        KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
         KC_CHECK(hipStreamSynchronize(s));
-        if (err) return KC_EINVAL;
+        if (invalid(hctl)) return KC_EINVAL;
     }
 
     // 1. sort keys
     if (order == KC_ORDER_DEGREE) {
-        k_degree_key<<<grid_for_threads(n), kBlock, 0, s>>>(n, g->row_ptr, w.key_a, w.val_a, w.ctl);
+        k_degree_key<<<grid_for_keys(n), kBlock, 0, s>>>(n, g->row_ptr, w.key_a, w.val_a, w.ctl, nullptr, 0, 0);
         KC_CHECK(hipGetLastError());
     } else if (order == KC_ORDER_COLOR) {
         // the colours go straight into the sort keys; rounds are launched in
@@ -1209,7 +1614,7 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
         KC_CHECK(hipMemcpyAsync(w.key_a, w.rnd, sizeof(int) * n, hipMemcpyDeviceToDevice, s));
     } else {
         int* deg = w.key_b;   // scratch until the sort
-        if (n > kCoreCap) {
+        if (n > kCoreSmall) {
             // one block per 16k vertices, between 16 and 64 (a barrier costs 0.8 us at
             // 16 blocks, 1.3 at 64, 3.7 at 256, whatever the block size)
             int occ = 0;
@@ -1239,50 +1644,21 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
         k_core_peel<<<1, kPeelBlock, lds, s>>>(span, rows, w.fr0, w.fr1, w.key_a, w.ctl);
         KC_CHECK(hipGetLastError());
     }
-    int hctl[CTL_WORDS];
-    KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
-    KC_CHECK(hipStreamSynchronize(s));
-    if (order == KC_ORDER_DEGENERACY && !hctl[CTL_DONE]) return KC_EDEVICE;   // a barrier wait ran out
-    int bits = 0;
-    while (bits < 31 && (hctl[CTL_MAXKEY] >> bits) != 0) bits++;
-
-    // 2. stable radix sort (key, id) -> position = new id
-    int ntiles = div_up(n, kTile);
-    int *kin = w.key_a, *vin = w.val_a, *kout = w.key_b, *vout = w.val_b;
-    for (int bit = 0; bit < bits; bit++) {
-        k_tile_sum<<<ntiles, kBlock, 0, s>>>(n, kin, bit, 1, w.tiles);
-        k_scan_tiles<<<1, kBlock, 0, s>>>(ntiles, w.tiles, w.ctl + CTL_ZEROS);
-        k_radix_scatter<<<ntiles, kBlock, 0, s>>>(n, bit, kin, vin, w.tiles, w.ctl + CTL_ZEROS, kout, vout);
-        KC_CHECK(hipGetLastError());
-        int* t = kin; kin = kout; kout = t;
-        t = vin; vin = vout; vout = t;
-    }
-    KC_CHECK(hipMemcpyAsync(out->perm, vin, sizeof(int) * n, hipMemcpyDeviceToDevice, s));
-    k_rank<<<grid_for_threads(n), kBlock, 0, s>>>(n, out->perm, w.rank);
-    KC_CHECK(hipGetLastError());
-
-    // 3. filter: out-degree histogram + exclusive scan -> row_ptr
-    k_outdeg<<<grid_for_waves(n), kBlock, 0, s>>>(n, g->row_ptr, g->col, out->perm, w.rank, w.outdeg, w.ctl);
-    KC_CHECK(hipGetLastError());
-    int st = exclusive_scan(n, w.outdeg, out->row_ptr, w.tiles, w.ctl + CTL_ZEROS, s);
+    // 2. stable radix sort (key, id) -> position = new id; 3. filter: out-degrees and
+    // their scan -> row_ptr; 4. compact + per-row sort.  Degrees and colours are below
+    // n; the peel's rounds below 2 n, as a level change counts as one.
+    int st = build_dag(w, n, nnz, g->row_ptr, g->col, order == KC_ORDER_DEGENERACY ? 2LL * n : n, false, out->row_ptr, out->col, out->src, out->perm, s);
     if (st != KC_OK) return st;
-
-    // 4. compact + per-row sort
-    if (m > 0) {
-        k_fill<<<grid_for_waves(n), kBlock, 0, s>>>(n, g->row_ptr, g->col, out->perm, w.rank, out->row_ptr,
-                                                   out->col, out->src, w.tmp, w.ctl);
-        KC_CHECK(hipGetLastError());
-    }
     KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
-    int total = 0;
-    KC_CHECK(hipMemcpyAsync(&total, out->row_ptr + n, sizeof(int), hipMemcpyDeviceToHost, s));
     KC_CHECK(hipStreamSynchronize(s));
+    if (invalid(hctl)) return KC_EINVAL;
+    if (order == KC_ORDER_DEGENERACY && !hctl[CTL_DONE]) return KC_EDEVICE;   // a barrier wait ran out
     if (hctl[CTL_LONG]) {
-        k_sort_long_rows<<<grid_for_threads(n), kBlock, 0, s>>>(n, out->row_ptr, w.tmp, out->col, out->src);
+        k_sort_long_rows<<<grid_for_threads(n), kBlock, 0, s>>>(n, out->row_ptr, w.tmp, out->col, out->src, w.ctl);
         KC_CHECK(hipGetLastError());
         KC_CHECK(hipStreamSynchronize(s));
     }
-    if (total != m) return KC_EINVAL;   // not symmetric (only possible without validation)
+    if (hctl[CTL_TOTAL] != m) return KC_EINVAL;   // not symmetric (only possible without validation)
     out->d_max = hctl[CTL_DMAX];
     out->degeneracy = order == KC_ORDER_DEGENERACY ? hctl[CTL_DEGEN] : -1;
     return KC_OK;

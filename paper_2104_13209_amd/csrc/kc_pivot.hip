@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(64 * WPB) k_piv(PivParams P) {
         unsigned int I = 0, Po = 0, Pr = 0;
         int np = 0, nh = nh_root, level = 0, p = 0;
         if (!roots_done) {
-            slot = claim_root<true>(rc, P.head, nroots, blockIdx.x * WPB + wv, gridDim.x * WPB,
+            slot = claim_root(rc, P.head, nroots, blockIdx.x * WPB + wv, gridDim.x * WPB,
                               MAXW <= 2 ? kPivRootChunkLight : kPivRootChunkHeavy);
             if (slot < 0) {
                 roots_done = true;
