@@ -80,39 +80,63 @@ __host__ __device__ inline TeamLayout team_layout(int s_cap, int maxw, int group
 
 // Split roots into light / heavy lists by the bound on |S|; drop roots whose
 // bound is below `need` (a k-clique needs |S| >= k - 1 for VC, >= k - 2 for EC).
+// Roots of at most mid_cap candidates that are not light go to the middle list,
+// which grows down from heavy[heavy_cap - 1] (mid_cap 0: there is none).  A wavefront
+// takes 512 roots between its three atomics on the list sizes.
 template <bool EC>
 __global__ void __launch_bounds__(kBlock) k_classify(int nroots_total, int need, const int* __restrict__ row_ptr,
                                                     const int* __restrict__ col, const int* __restrict__ src,
-                                                    int* light, int* heavy, int* ctl) {
+                                                    int* light, int* heavy, int heavy_cap, int mid_cap, int* ctl) {
+    constexpr int U = 8;
     const int lane = threadIdx.x & 63;
-    for (int base = blockIdx.x * blockDim.x; base < nroots_total; base += gridDim.x * blockDim.x) {
-        int r = base + threadIdx.x;
-        int bound = -1;
-        if (r < nroots_total) {
-            if (EC) {
-                int u = src[r], v = col[r];
-                int du = row_ptr[u + 1] - row_ptr[u] - 1;
-                int dv = row_ptr[v + 1] - row_ptr[v];
-                bound = du < dv ? du : dv;
-                if (du >= KC_MAX_DMAX) bound = -1;   // a wide root
-            } else {
-                bound = row_ptr[r + 1] - row_ptr[r];
-                if (bound > KC_MAX_DMAX) bound = -1;                          // a wide root
+    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, nwaves = (gridDim.x * blockDim.x) >> 6;
+    for (long long base = static_cast<long long>(wave) * 64 * U; base < nroots_total;
+         base += static_cast<long long>(nwaves) * 64 * U) {
+        int cls[U];                                     // 0 light, 1 heavy, 2 middle, -1 dropped
+        int n[3] = {0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < U; i++) {
+            const long long rr = base + 64 * i + lane;
+            const int r = static_cast<int>(rr);
+            int bound = -1;
+            if (rr < nroots_total) {
+                if (EC) {
+                    int u = src[r], v = col[r];
+                    int du = row_ptr[u + 1] - row_ptr[u] - 1;
+                    int dv = row_ptr[v + 1] - row_ptr[v];
+                    bound = du < dv ? du : dv;
+                    if (du >= KC_MAX_DMAX) bound = -1;   // a wide root
+                } else {
+                    bound = row_ptr[r + 1] - row_ptr[r];
+                    if (bound > KC_MAX_DMAX) bound = -1;                          // a wide root
+                }
+            }
+            cls[i] = bound < need || bound < 0 ? -1 : bound <= kLightCap ? 0 : bound <= mid_cap ? 2 : 1;
+#pragma unroll
+            for (int c = 0; c < 3; c++) n[c] += __popcll(__ballot(cls[i] == c));
+        }
+        int at = 0;
+        if (lane < 3 && n[lane == 0 ? 0 : lane == 1 ? 1 : 2])
+            at = atomicAdd(&ctl[lane == 0 ? CC_LIGHT_N : lane == 1 ? CC_HEAVY_N : CC_MID_N],
+                           n[lane == 0 ? 0 : lane == 1 ? 1 : 2]);
+        int pos[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) pos[c] = __shfl(at, c);
+#pragma unroll
+        for (int i = 0; i < U; i++) {
+            const int r = static_cast<int>(base + 64 * i + lane);
+#pragma unroll
+            for (int c = 0; c < 3; c++) {
+                const unsigned long long m = __ballot(cls[i] == c);
+                const int p = pos[c] + __popcll(m & lanemask_lt());
+                if (cls[i] == c) {
+                    if (c == 0) light[p] = r;
+                    else if (c == 1) heavy[p] = r;
+                    else heavy[heavy_cap - 1 - p] = r;
+                }
+                pos[c] += __popcll(m);
             }
         }
-        bool ok = r < nroots_total && bound >= need && bound >= 0;
-        bool is_light = ok && bound <= kLightCap;
-        bool is_heavy = ok && bound > kLightCap;
-        unsigned long long ml = __ballot(is_light), mh = __ballot(is_heavy);
-        int bl = 0, bh = 0;
-        if (lane == 0) {
-            if (ml) bl = atomicAdd(&ctl[CC_LIGHT_N], __popcll(ml));
-            if (mh) bh = atomicAdd(&ctl[CC_HEAVY_N], __popcll(mh));
-        }
-        bl = __shfl(bl, 0);
-        bh = __shfl(bh, 0);
-        if (is_light) light[bl + __popcll(ml & lanemask_lt())] = r;
-        if (is_heavy) heavy[bh + __popcll(mh & lanemask_lt())] = r;
     }
 }
 
@@ -620,9 +644,10 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
     KC_CHECK(hipMemcpyAsync(w.acc, init, sizeof(init), hipMemcpyHostToDevice, s));
     if (pivot_all >= 0) {
         KC_CHECK(hipMemsetAsync(w.counts, 0, 2 * sizeof(unsigned long long) * w.counts_len, s));
-        // frame queues of the light and the heavy launch
-        KC_CHECK(hipMemsetAsync(w.qctl, 0, sizeof(int) * kQueueCtlWords * 2, s));
-        KC_CHECK(hipMemsetAsync(w.qready, 0, sizeof(int) * kQueueCap * 2, s));
+        // frame queues of the light, the heavy and the middle launch
+        KC_CHECK(hipMemsetAsync(w.qctl, 0, sizeof(int) * kQueueCtlTotal, s));
+        KC_CHECK(hipMemsetAsync(w.qready, 0, sizeof(int) * kQueueCap * 3, s));
+        KC_CHECK(hipMemsetAsync(w.leaves, 0, sizeof(unsigned long long) * w.leaf_count, s));
         int st0 = pivot_binom_table(w, s);
         if (st0 != KC_OK) return st0;
     }
@@ -632,6 +657,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
     int cblocks = div_up(nroots, kBlock);
     if (cblocks > device_cus() * 8) cblocks = device_cus() * 8;
     if (cblocks < 1) cblocks = 1;
+    const int mid_cap = pivot_all == 0 || pivot_all == 1 ? kMidCap : 0;   // totals: the middle list
     const bool lists = pivot_all < 0 && o && (o->flags & KC_OPT_NO_BITSETS);
     bool lane_path = pivot_all < 0 && !lists && (o ? o->width : 0) <= 1;
     if (lane_path) {
@@ -660,9 +686,10 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             k_classify_w<false, false><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.ctl, w.heavy);
         }
     } else if (ec) {
-        k_classify<true><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.heavy, w.ctl);
+        k_classify<true><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.heavy, w.nroots_cap, mid_cap, w.ctl);
     } else {
-        k_classify<false><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.heavy, w.ctl);
+        k_classify<false><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.heavy, w.nroots_cap,
+                                                    mid_cap, w.ctl);
     }
     KC_CHECK(hipGetLastError());
     if (prof && !lane_path) KC_CHECK(hipEventRecord(pe->ev[1], s));
@@ -815,12 +842,30 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         L.col = d->col;
         L.src = d->src;
         L.w = w;
-        st = pivot_launch(L, false, s);
-        if (st != KC_OK) return st;
-        if (prof) KC_CHECK(hipEventRecord(pe->ev[2], s));
-        if (dm > kLightCap) {
-            st = pivot_launch(L, true, s);
+        if (mid_cap > 0) {
+            // totals: search state in registers for up to kMidCap candidates; queue
+            // items of the middle and the heavy launch share a region in turn
+            st = pivot_reg_launch(L, false, s);
             if (st != KC_OK) return st;
+            if (prof) KC_CHECK(hipEventRecord(pe->ev[2], s));
+            if (dm > kLightCap) {
+                st = pivot_reg_launch(L, true, s);
+                if (st != KC_OK) return st;
+            }
+            if (dm > mid_cap) {
+                st = pivot_launch(L, true, s);
+                if (st != KC_OK) return st;
+            }
+            st = pivot_leaves_launch(L, s);
+            if (st != KC_OK) return st;
+        } else {
+            st = pivot_launch(L, false, s);
+            if (st != KC_OK) return st;
+            if (prof) KC_CHECK(hipEventRecord(pe->ev[2], s));
+            if (dm > kLightCap) {
+                st = pivot_launch(L, true, s);
+                if (st != KC_OK) return st;
+            }
         }
     }
     if (d->d_max > KC_MAX_DMAX && !lists && pivot_all != 2) {
@@ -900,7 +945,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             }
         } else {
             prof->light_roots = hctl[CC_LIGHT_N];
-            prof->heavy_roots = hctl[CC_HEAVY_N];
+            prof->heavy_roots = hctl[CC_HEAVY_N] + hctl[CC_MID_N];
         }
     }
     return KC_OK;

@@ -6,6 +6,10 @@
 namespace kc {
 
 constexpr int kLightCap = 64;          // |S| bound of the light root list
+constexpr int kMidCap = 128;           // and of the pivot's middle list
+
+// Pivot leaf counters: leaves with nh holds among t = holds + pivots vertices.
+constexpr __host__ __device__ int leaf_index(int t, int nh) { return t * (t + 1) / 2 + nh; }
 constexpr int kPivBlocksPerCU = 8;     // grid cap of the heavy pivot kernel (sizes its stacks)
 constexpr int kLaneWavesPerCU = 32;    // grid cap of the lane-walk kernel (sizes its registry)
 constexpr int kWidthLists = 6;         // root lists by bitset words per row: 1, 2, 4, 8, 16, 32
@@ -21,6 +25,7 @@ constexpr int Q_HEAD = 0, Q_TAIL = 1, Q_PENDING = 2, Q_ROOTING = 3, Q_HUNGRY = 4
 constexpr int kMaxWaiters = 256;                            // wavefronts that wait for handed-over work
 constexpr unsigned long long kStallTicks = 2000000000ull;   // 20 s at 100 MHz without queue progress
 constexpr int kReadySpins = 1 << 22;                        // wait for a reserved item's sequence word
+constexpr int kQueueCtlTotal = 3 * 8 * 32;   // the most any path uses: three sharded pivot queues
 // bits of the CC_FLAGS control word
 constexpr int kFlagBigBinom = 1;    // a binomial beyond 128 bits was used
 constexpr int kFlagStalled = 2;     // a work queue stopped making progress (no valid count)
@@ -44,6 +49,13 @@ constexpr int kPivStealAfterLightEC = 65536;
 // CU, 930 / 665 at 4, 1240 / 775 at 8, 3000 / 1390 at 16 (handoffs and queue
 // traffic then outweigh the overlap); 810 / 650 at 4 per CU with 8192.
 constexpr int kPivWaitersPerCU = 4;
+// Pivot walks in registers: independent frame queues, 128 bytes between their control
+// words; nodes between looks and before the first handoff; waiting wavefronts.
+constexpr int kRegShards = 8;
+constexpr int kShardLine = 32;
+constexpr int kRegStealEvery = 256;
+constexpr int kRegStealAfter = 1024;
+constexpr int kRegWaitersPerCU = 32;
 constexpr int kCancelEvery = 32;       // wavefront rounds (lane walk) or nodes (pivot) between cancel polls
 // count lo/hi, light/heavy stats, per width list: nodes, words, iterations,
 // expansions, busy, start, end; helper timing (3); per width list: counted
@@ -67,6 +79,8 @@ enum CountCtl {
     CC_FLAGS = 4,        // kFlag* bits
     CC_WIDE_N = 5,       // wide root count
     CC_WIDE_HEAD = 6,    // wide queue head
+    CC_MID_N = 7,        // pivot: middle root count
+    CC_MID_HEAD = 14,    // pivot: middle queue head
     CC_WN0 = 8,          // width lists: root counts (8..13)
     CC_WC0 = 16,         // width lists: fill cursors (16..21)
     CC_WH0 = 24,         // width lists: queue heads (24..29)
@@ -172,7 +186,10 @@ struct CountWs {
     int* ctl;
     unsigned long long* acc;      // [lo, hi, light nodes, words, heavy nodes, words, then per width list nodes, words]
     int* light;
-    int* heavy;
+    int* heavy;                   // pivot: the middle list grows down from its end
+    int nroots_cap;               // entries of light and of heavy
+    unsigned long long* leaves;   // pivot: leaf counters, and how many
+    int leaf_count;
     unsigned long long* counts;   // count_all: (binom_n + 1) x {lo, hi}
     unsigned long long* binom;    // (binom_n + 1)^2 x {lo, hi}: C(i, j) at [i * (binom_n + 1) + j]
     unsigned char* big;           // same shape: 1 if C(i, j) needs more than 128 bits
@@ -202,11 +219,12 @@ inline CountWs carve_count(void* ws, const kc_dag* d, bool pivot, size_t* bytes)
     w.acc = c.take<unsigned long long>(kAccTotal);
     w.light = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.heavy = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
+    w.nroots_cap = nr > 0 ? nr : 1;
     w.task_ctr = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.task_tot = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.nactive = device_cus() * kLaneWavesPerCU;
     w.active = c.take<int>(2 * static_cast<size_t>(w.nactive));    // main and side stream
-    w.qctl = c.take<int>(kQueueCtlWords * kWidthLists);
+    w.qctl = c.take<int>(kQueueCtlTotal);
     w.qready = c.take<int>(static_cast<size_t>(kQueueCap) * kQueueLists);
     w.qitems = c.take<unsigned int>(2 * static_cast<size_t>(kQueueCap) * kItemWords);   // main and side stream
     const int dm = bit_dmax(d->d_max);
@@ -219,7 +237,9 @@ inline CountWs carve_count(void* ws, const kc_dag* d, bool pivot, size_t* bytes)
         w.counts = c.take<unsigned long long>(2 * static_cast<size_t>(w.counts_len));
         w.binom = c.take<unsigned long long>(2 * cells);
         w.big = c.take<unsigned char>(cells);
-        if (dm > kLightCap) {
+        w.leaf_count = leaf_index((dm < kMidCap ? dm : kMidCap) + 3, 0);
+        w.leaves = c.take<unsigned long long>(static_cast<size_t>(w.leaf_count));
+        if (dm > kMidCap) {   // smaller roots keep their stacks on chip
             const int maxw = maxw_for(dm);
             w.slab_words = static_cast<size_t>(s_cap + 2) * piv_level_words(maxw);
             w.slabs = device_cus() * kPivBlocksPerCU * 4;
@@ -268,6 +288,12 @@ struct PivLaunch {
 
 int pivot_binom_table(const CountWs& w, hipStream_t s);
 int pivot_launch(const PivLaunch& L, bool heavy, hipStream_t s);
+
+// Roots of at most kLightCap (light) or kMidCap (mid) candidates with the search state
+// in registers (kc_pivot_reg.hip): leaves go to w.leaves, which the last launch
+// turns into counts.
+int pivot_reg_launch(const PivLaunch& L, bool mid, hipStream_t s);
+int pivot_leaves_launch(const PivLaunch& L, hipStream_t s);
 
 // Launch description for the lane-walk graph-orientation kernel (kc_lane.hip).
 struct LaneLaunch {

@@ -30,7 +30,7 @@ namespace kc {
 namespace {
 
 // Most roots claimed at once: light roots (at most 64 candidates), heavy ones.
-constexpr int kPivRootChunkLight = 4, kPivRootChunkHeavy = 1;
+constexpr int kPivRootChunkLight = 4, kPivRootChunkHeavy = 1;   // also those of kc_pivot_reg.hip
 
 struct PivParams {
     int k;
@@ -588,10 +588,13 @@ int launch_piv_t(PivParams P, bool stats, int grid_cap_per_cu, hipStream_t s) {
 
 template <int MAXW, bool GST, int WPB, bool EC>
 int launch_piv_e(const PivParams& P, int mode, bool stats, int cap, hipStream_t s) {
+    if constexpr (MAXW > 4) {   // totals of smaller roots: kc_pivot_reg.hip
+        if (mode == 0) return launch_piv_t<MAXW, EC, 0, GST, WPB>(P, stats, cap, s);
+        if (mode == 1) return launch_piv_t<MAXW, EC, 1, GST, WPB>(P, stats, cap, s);
+    }
     switch (mode) {
-        case 0: return launch_piv_t<MAXW, EC, 0, GST, WPB>(P, stats, cap, s);
-        case 1: return launch_piv_t<MAXW, EC, 1, GST, WPB>(P, stats, cap, s);
-        default: return launch_piv_t<MAXW, EC, 2, GST, WPB>(P, stats, cap, s);
+        case 2: return launch_piv_t<MAXW, EC, 2, GST, WPB>(P, stats, cap, s);
+        default: return KC_EINVAL;
     }
 }
 
