@@ -292,7 +292,7 @@ extern "C" KC_API int32_t kc_batch_count(const kc_batch* b, int32_t k, uint64_t*
             LaneLaunch L;
             L.k = k;
             L.ec = ec;
-            L.pair = deep && lst >= 1;
+            L.pair = pair_list(k, ec, lst);
             L.stats = false;
             L.maxw = 1 << lst;
             L.list = lst;

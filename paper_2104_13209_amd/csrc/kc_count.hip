@@ -664,8 +664,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         // the widest list must fit one wavefront's LDS; otherwise use the group walk
         int top = 0;
         while (top < kWidthLists - 1 && (32 << top) < dm) top++;
-        const bool deep = k >= (ec ? 3 : 2) + 4;
-        if (lane_lds_bytes(1 << top, k, ec, deep && top >= 1) > 160 * 1024) lane_path = false;
+        if (lane_lds_bytes(1 << top, k, ec, pair_list(k, ec, top)) > 160 * 1024) lane_path = false;
     }
     if (lane_path) {
         KC_CHECK(hipMemsetAsync(w.active, 0xff, 2 * sizeof(int) * w.nactive, s));
@@ -727,7 +726,7 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             LaneLaunch L;
             L.k = k;
             L.ec = ec;
-            L.pair = deep && lst >= 1;
+            L.pair = pair_list(k, ec, lst);
             L.stats = stats;
             L.maxw = 1 << lst;
             L.list = lst;
@@ -972,8 +971,7 @@ size_t count_lds_demand(const kc_dag* d, int k, int pivot) {
     if (!pivot) {
         int top = 0;
         while (top < kWidthLists - 1 && (32 << top) < dm) top++;
-        const bool deep = k >= (ec ? 3 : 2) + 4;
-        per_wave = lane_lds_bytes(1 << top, k, ec, deep && top >= 1);
+        per_wave = lane_lds_bytes(1 << top, k, ec, pair_list(k, ec, top));
         waves = static_cast<long long>(device_cus()) * kLaneWavesPerCU;
     } else {
         const int s_cap = s_cap_for(dm), maxw = maxw_for(dm);

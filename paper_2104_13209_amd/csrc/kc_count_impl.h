@@ -384,6 +384,16 @@ int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, cons
                         int max_degree, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, void* ws,
                         hipStream_t s, bool* grouped);
 
+// Whether a width list runs by pair tasks: trees four levels deep from the second
+// vertex task on (shallower ones are counted from vertex tasks), except that roots of
+// at most 64 candidates are walked by vertex tasks at the least of these depths: their
+// trees are too small to pay for the pair counters (list 1 of k = 7 with edge roots on a
+// 1M-vertex power-law graph: 21 ms by pairs, 14.5 by vertices; at k = 8, 23.6 and 26.2).
+inline bool pair_list(int k, bool ec, int list) {
+    const int deep = (ec ? 3 : 2) + 4;
+    return list >= 2 ? k >= deep : list == 1 && k > deep;
+}
+
 // LDS bytes one lane-walk wavefront needs for a list of `maxw` words per row.
 inline size_t lane_lds_bytes(int maxw, int k, bool ec, bool pair) {
     const int s_cap = 32 * maxw;

@@ -32,11 +32,11 @@ namespace kc {
 namespace lanewalk {
 
 constexpr int kPairChunk = 64;    // pair tasks claimed per global atomic
-// Most roots claimed at once: vertex-task lists have many small roots, pair-task
-// lists few large ones (8 at a time left wavefronts with several dense-core
-// roots each: k = 10 on the 1M-vertex power-law graph 460 -> 525 ms).
-constexpr int kRootChunk = 32;
-constexpr int kPairRootChunk = 1;
+// Most roots claimed at once: many where rows are one word, few at two, one where roots
+// may be large (two thirds of a share at once left wavefronts with several of the
+// largest: the 8-word list of a k = 4 count 1.6 -> 2.3 ms; pair tasks eight at a time,
+// k = 10 460 -> 525 ms).
+__host__ __device__ constexpr int root_chunk(int maxw, bool pair) { return pair || maxw >= 4 ? 1 : maxw == 2 ? 8 : 32; }
 constexpr int kInner = 8;         // lane-local steps per wavefront-level round
 constexpr int kStealMax = 8;      // subtrees handed over per look
 
@@ -87,9 +87,14 @@ __device__ __forceinline__ bool poll_cancel(const int* cancel, int* flags) {
 // Batched counts: the lanes' partial counts of one root belong to one graph; add
 // them to that graph's 128-bit counter and restart from zero.
 __device__ __forceinline__ void flush_root(const LaneParams& P, int g, unsigned long long& acc) {
-    unsigned long long lo, hi;
-    wave_sum_u128(acc, lo, hi);
-    if (__lane_id() == 0 && (lo | hi)) atomic_add_u128(P.gacc + 2 * g, P.gacc + 2 * g + 1, lo, hi);
+    if (__ballot(acc != 0ull) == 0ull) return;
+    unsigned long long lo, hi = 0;
+    if (__ballot((acc >> 25) != 0ull) == 0ull) {
+        lo = static_cast<unsigned int>(wave_sum_dpp(static_cast<int>(acc)));   // below 2^31
+    } else {
+        wave_sum_u128(acc, lo, hi);
+    }
+    if (__lane_id() == 0) atomic_add_u128(P.gacc + 2 * g, P.gacc + 2 * g + 1, lo, hi);
     acc = 0;
 }
 
@@ -635,7 +640,7 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
     for (;;) {
         int slot = -1;
         if (!helping) {
-            slot = claim_root(rc, P.head, nroots, blockIdx.x, nwaves, PAIR ? kPairRootChunk : kRootChunk);
+            slot = claim_root(rc, P.head, nroots, blockIdx.x, nwaves, root_chunk(MAXW, PAIR));
             if (slot < 0) {
                 if (PAIR) helping = true;
                 else break;
