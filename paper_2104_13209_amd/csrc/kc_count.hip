@@ -704,15 +704,14 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             k_classify_w<false, true><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.ctl, w.heavy);
         KC_CHECK(hipGetLastError());
         if (prof) KC_CHECK(hipEventRecord(pe->ev[1], s));
-        const int p0 = ec ? 3 : 2;
-        const bool deep = k >= p0 + 4;
         int top = 0;
         while (top < kWidthLists - 1 && (32 << top) < dm) top++;
-        // deep trees: the widest list runs on a side stream beside the others, so
-        // that the tail of its few large roots overlaps their work
+        // pair tasks: the widest list runs on a side stream beside the others, so
+        // that the tail of its few large roots overlaps their work.  (A list of vertex
+        // tasks must be launched once: its first chunks are fixed by wavefront index.)
         SideGuard side;
         LaneLaunch side_launch;
-        if (deep && top >= 1 && !(o && (o->flags & KC_OPT_SINGLE_STREAM))) {
+        if (pair_list(k, ec, top) && !(o && (o->flags & KC_OPT_SINGLE_STREAM))) {
             st = side_acquire(&side.s);
             if (st != KC_OK) return st;
             side.held = true;
