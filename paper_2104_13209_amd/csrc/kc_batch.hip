@@ -12,7 +12,7 @@
 // synchronisation, no memset and no device allocation happen inside the call.
 #include <cmath>
 
-#include "kc_count_impl.h"
+#include "kc_classify.h"
 
 namespace kc {
 namespace {
@@ -68,56 +68,26 @@ __global__ void __launch_bounds__(kBlock) k_small_k(int ngraphs, int k, const in
     }
 }
 
-__device__ __forceinline__ int width_list_b(int bound) {
-    return bound <= 32 ? 0 : bound <= 64 ? 1 : bound <= 128 ? 2 : bound <= 256 ? 3 : bound <= 512 ? 4 : 5;
-}
-
-// Width-list classification of the roots of graphs whose size bucket is in
-// `buckets` (a bit mask): pass 1 counts, pass 2 appends (as in the single-graph
-// path).
-template <bool EC, bool FILL>
-__global__ void __launch_bounds__(kBlock) k_classify_batch(int nroots_total, int need, const int* __restrict__ row_ptr,
-                                                          const int* __restrict__ col, const int* __restrict__ src,
-                                                          const int* __restrict__ gid,
-                                                          const unsigned char* __restrict__ bucket, unsigned buckets,
-                                                          int* lists, int* ctl) {
-    const int lane = threadIdx.x & 63;
-    int off[kWidthLists];
-    if (FILL) {
-        int run = 0;
-        for (int j = 0; j < kWidthLists; j++) {
-            off[j] = run;
-            run += ctl[CC_WN0 + j];
+// Width lists of the roots of graphs whose size bucket is in `buckets` (a bit mask),
+// by the size bound of S.
+template <bool EC>
+struct BatchLists {
+    int need;
+    unsigned buckets;
+    const int *row_ptr, *col, *src, *gid;
+    const unsigned char* bucket;
+    __device__ __forceinline__ int operator()(int r) const {
+        const int u = EC ? src[r] : r;
+        int bound = row_ptr[u + 1] - row_ptr[u];
+        if (EC) {
+            const int v = col[r];
+            const int dv = row_ptr[v + 1] - row_ptr[v];
+            bound = bound - 1 < dv ? bound - 1 : dv;
         }
+        if (bound < need || bound < 0) return -1;
+        return (buckets >> bucket[gid[u]]) & 1u ? width_list(bound) : -1;
     }
-    for (int base = blockIdx.x * blockDim.x; base < nroots_total; base += gridDim.x * blockDim.x) {
-        const int r = base + threadIdx.x;
-        int lst = -1;
-        if (r < nroots_total) {
-            const int u = EC ? src[r] : r;
-            if ((buckets >> bucket[gid[u]]) & 1u) {
-                int bound;
-                if (EC) {
-                    const int v = col[r];
-                    const int du = row_ptr[u + 1] - row_ptr[u] - 1;
-                    const int dv = row_ptr[v + 1] - row_ptr[v];
-                    bound = du < dv ? du : dv;
-                } else {
-                    bound = row_ptr[u + 1] - row_ptr[u];
-                }
-                if (bound >= need && bound >= 0) lst = width_list_b(bound);
-            }
-        }
-        for (int j = 0; j < kWidthLists; j++) {
-            const unsigned long long m = __ballot(lst == j);
-            if (m == 0ull) continue;
-            int b = 0;
-            if (lane == 0) b = atomicAdd(&ctl[(FILL ? CC_WC0 : CC_WN0) + j], __popcll(m));
-            b = __shfl(b, 0);
-            if (FILL && lst == j) lists[off[j] + b + __popcll(m & lanemask_lt())] = r;
-        }
-    }
-}
+};
 
 struct BatchWs {
     void* orient_ws;
@@ -126,6 +96,7 @@ struct BatchWs {
     int* ctl[2];               // control words of alternate passes
     int* lists[2];
     int *task_ctr, *task_tot, *active;
+    int* bcnt;
     unsigned long long* acc;
     int nactive;
 };
@@ -151,6 +122,7 @@ BatchWs carve_batch(void* ws, const kc_batch* b, size_t* bytes) {
     w.nactive = device_cus() * kLaneWavesPerCU;
     w.active = c.take<int>(static_cast<size_t>(w.nactive));
     w.acc = c.take<unsigned long long>(kAccTotal);
+    w.bcnt = c.take<int>(kWidthLists * kListBlocks);
     *bytes = c.bytes();
     return w;
 }
@@ -253,18 +225,13 @@ extern "C" KC_API int32_t kc_batch_count(const kc_batch* b, int32_t k, uint64_t*
             k_fill_i32<<<grid_for(nroots), kBlock, 0, s>>>(w.task_ctr, 0, nroots);
             k_fill_i32<<<grid_for(nroots), kBlock, 0, s>>>(w.task_tot, 0, nroots);
         }
-        if (ec) {
-            k_classify_batch<true, false><<<grid_for(nroots), kBlock, 0, s>>>(
-                nroots, need_s, w.dag_row_ptr, w.dag_col, w.dag_src, w.gid, w.bucket, buckets, w.lists[pass], ctl);
-            k_classify_batch<true, true><<<grid_for(nroots), kBlock, 0, s>>>(
-                nroots, need_s, w.dag_row_ptr, w.dag_col, w.dag_src, w.gid, w.bucket, buckets, w.lists[pass], ctl);
-        } else {
-            k_classify_batch<false, false><<<grid_for(nroots), kBlock, 0, s>>>(
-                nroots, need_s, w.dag_row_ptr, w.dag_col, w.dag_src, w.gid, w.bucket, buckets, w.lists[pass], ctl);
-            k_classify_batch<false, true><<<grid_for(nroots), kBlock, 0, s>>>(
-                nroots, need_s, w.dag_row_ptr, w.dag_col, w.dag_src, w.gid, w.bucket, buckets, w.lists[pass], ctl);
-        }
-        KC_CHECK(hipGetLastError());
+        if (ec)
+            st = lists_launch_widths(BatchLists<true>{need_s, buckets, w.dag_row_ptr, w.dag_col, w.dag_src, w.gid, w.bucket},
+                                     nroots, w.bcnt, w.lists[pass], ctl, s);
+        else
+            st = lists_launch_widths(BatchLists<false>{need_s, buckets, w.dag_row_ptr, w.dag_col, w.dag_src, w.gid, w.bucket},
+                                     nroots, w.bcnt, w.lists[pass], ctl, s);
+        if (st != KC_OK) return st;
         if (width >= 2) {
             // sub-wavefront groups (Sec. 3.5), widest list first
             for (int lst = top; lst >= 0; lst--) {

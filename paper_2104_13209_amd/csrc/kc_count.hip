@@ -27,10 +27,12 @@
 // into a 128-bit device counter when they exit.
 #include <algorithm>
 #include <climits>
+#include <cstring>
 #include <mutex>
 #include <new>
 
 #include "kc_extract.h"
+#include "kc_classify.h"
 #include "kc_count_impl.h"
 
 namespace kc {
@@ -140,24 +142,12 @@ __global__ void __launch_bounds__(kBlock) k_classify(int nroots_total, int need,
     }
 }
 
-// Width lists: root r goes to list w when its |S| needs 2^w words per bitset
-// row (1, 2, 4, 8, 16 or 32); pass 1 counts, pass 2 appends into consecutive
-// segments of one array (the order inside a list is unspecified).
-__device__ __forceinline__ int width_list(int bound) {
-    return bound <= 32 ? 0 : bound <= 64 ? 1 : bound <= 128 ? 2 : bound <= 256 ? 3 : bound <= 512 ? 4 : 5;
-}
-
-// |S| of root r: |N+(u)| for a vertex root; for the edge root (u, v) the size
-// of N+(u) ∩ N+(v), counted exactly (rows are ascending, and every common
-// vertex lies after v in the row of u).  Sizes below `need` are only bounded.
-// Wide roots (first vertex with more than KC_MAX_DMAX out-neighbours) give -1.
-template <bool EC>
-__device__ __forceinline__ int root_size(int r, int need, const int* __restrict__ row_ptr,
-                                         const int* __restrict__ col, const int* __restrict__ src) {
-    if (!EC) {
-        const int s = row_ptr[r + 1] - row_ptr[r];
-        return s > KC_MAX_DMAX ? -1 : s;
-    }
+// |S| of the edge root r = (u, v): the size of N+(u) ∩ N+(v), counted exactly (rows
+// are ascending, and every common vertex lies after v in the row of u).  Sizes below
+// `need` are only bounded.  Wide roots (first vertex with more than KC_MAX_DMAX
+// out-neighbours) give -1.
+__device__ __forceinline__ int edge_root_size(int r, int need, const int* __restrict__ row_ptr,
+                                              const int* __restrict__ col, const int* __restrict__ src) {
     const int u = src[r], v = col[r];
     if (row_ptr[u + 1] - row_ptr[u] > KC_MAX_DMAX) return -1;
     const int a0 = r + 1, na = row_ptr[u + 1] - a0;
@@ -183,21 +173,16 @@ __device__ __forceinline__ int root_size(int r, int need, const int* __restrict_
 // row N+(u) is staged in LDS, then four 16-lane groups take the row's edges in
 // turn; a group reads N+(v) coalesced and binary-searches each entry in the tail
 // of N+(u) past v.  lst_of[r] gets the root's width list (-1 when |S| < need,
-// and for the wide roots of rows longer than KC_MAX_DMAX); the list sizes go to
-// ctl[CC_WN0 + j].  cap >= the longest DAG row up to KC_MAX_DMAX.
+// and for the wide roots of rows longer than KC_MAX_DMAX).  cap >= the longest DAG row up to KC_MAX_DMAX.
 constexpr int kSizeWaves = 4;   // wavefronts per block
 __global__ void __launch_bounds__(64 * kSizeWaves) k_sizes_ec(int n, int need, const int* __restrict__ row_ptr,
                                                              const int* __restrict__ col,
-                                                             const int* __restrict__ src, int* lst_of, int* ctl,
-                                                             int cap) {
+                                                             const int* __restrict__ src, int* lst_of, int cap) {
     extern __shared__ int su_all[];
     const int lane = threadIdx.x & 63;
     int* su = su_all + (threadIdx.x >> 6) * cap;
     const int g = lane >> 4, gl = lane & 15;
     const unsigned long long gmask = 0xFFFFull << (16 * g);
-    int cnt[kWidthLists];
-#pragma unroll
-    for (int q = 0; q < kWidthLists; q++) cnt[q] = 0;
     const int nw = gridDim.x * kSizeWaves;
     for (int u = blockIdx.x * kSizeWaves + static_cast<int>(threadIdx.x >> 6); u < n; u += nw) {
         const int b = row_ptr[u], du = row_ptr[u + 1] - b;
@@ -209,10 +194,8 @@ __global__ void __launch_bounds__(64 * kSizeWaves) k_sizes_ec(int n, int need, c
         if (du > cap) {
             // a row longer than the stated d_max: per-edge search in global memory
             for (int i = lane; i < du; i += 64) {
-                const int size = root_size<true>(b + i, need, row_ptr, col, src);
+                const int size = edge_root_size(b + i, need, row_ptr, col, src);
                 const int lst = size >= need ? width_list(size) : -1;
-#pragma unroll
-                for (int q = 0; q < kWidthLists; q++) cnt[q] += lst == q;
                 lst_of[b + i] = lst;
             }
             continue;
@@ -249,55 +232,26 @@ __global__ void __launch_bounds__(64 * kSizeWaves) k_sizes_ec(int n, int need, c
             }
             if (gl == 0 && j < du) {
                 const int lst = live && hits >= need ? width_list(hits) : -1;
-#pragma unroll
-                for (int q = 0; q < kWidthLists; q++) cnt[q] += lst == q;
                 lst_of[b + j] = lst;
             }
         }
         wave_sync_lds();
     }
-#pragma unroll
-    for (int q = 0; q < kWidthLists; q++) {
-        const int tot = wave_sum(cnt[q]);
-        if (lane == 0 && tot) atomicAdd(&ctl[CC_WN0 + q], tot);
-    }
 }
 
-template <bool EC, bool FILL>
-__global__ void __launch_bounds__(kBlock) k_classify_w(int nroots_total, int need, const int* __restrict__ row_ptr,
-                                                      const int* __restrict__ col, const int* __restrict__ src,
-                                                      int* lists, int* ctl, int* lst_of) {
-    const int lane = threadIdx.x & 63;
-    int off[kWidthLists];
-    if (FILL) {
-        int run = 0;
-        for (int j = 0; j < kWidthLists; j++) {
-            off[j] = run;
-            run += ctl[CC_WN0 + j];
-        }
+// Lists of vertex roots, and of edge roots whose sizes k_sizes_ec has listed.
+struct VertexLists {
+    int need;
+    const int* row_ptr;
+    __device__ __forceinline__ int operator()(int r) const {
+        const int size = row_ptr[r + 1] - row_ptr[r];
+        return size >= need && size >= 0 && size <= KC_MAX_DMAX ? width_list(size) : -1;
     }
-    for (int base = blockIdx.x * blockDim.x; base < nroots_total; base += gridDim.x * blockDim.x) {
-        const int r = base + threadIdx.x;
-        int lst = -1;
-        if (r < nroots_total) {
-            if (FILL) {
-                lst = lst_of[r];                    // from the counting pass
-            } else {
-                const int size = root_size<EC>(r, need, row_ptr, col, src);
-                if (size >= need && size >= 0) lst = width_list(size);
-                lst_of[r] = lst;
-            }
-        }
-        for (int j = 0; j < kWidthLists; j++) {
-            const unsigned long long m = __ballot(lst == j);
-            if (m == 0ull) continue;
-            int b = 0;
-            if (lane == 0) b = atomicAdd(&ctl[(FILL ? CC_WC0 : CC_WN0) + j], __popcll(m));
-            b = __shfl(b, 0);
-            if (FILL && lst == j) lists[off[j] + b + __popcll(m & lanemask_lt())] = r;
-        }
-    }
-}
+};
+struct EdgeLists {
+    const int* lst_of;
+    __device__ __forceinline__ int operator()(int r) const { return lst_of[r]; }
+};
 
 // ------------------------------------------------------------- traversal
 
@@ -615,6 +569,40 @@ int pick_width(const kc_opts* o, int d_max, bool light) {
     return w;
 }
 
+// Ranges of ints that one launch sets, instead of a memset each: a small count waited
+// longer for the memsets and copies between its launches than for the launches.
+struct Clear {
+    static constexpr int kMost = 6;
+    int* p[kMost];
+    long long n[kMost];
+    int v[kMost];
+    int jobs = 0;
+    template <class T>
+    void add(T* at, long long ints, int value) {
+        p[jobs] = reinterpret_cast<int*>(at);
+        n[jobs] = ints;
+        v[jobs++] = value;
+    }
+    int grid() const {
+        long long most = kAccTotal;
+        for (int j = 0; j < jobs; j++) most = n[j] > most ? n[j] : most;
+        const long long blocks = (most + kBlock - 1) / kBlock, cap = device_cus() * 8LL;
+        return static_cast<int>(blocks < cap ? blocks : cap);
+    }
+};
+
+// acc: zero, but for the count's start and the lists' earliest start times.
+__global__ void __launch_bounds__(kBlock) k_clear(Clear c, unsigned long long* acc, unsigned long long preload) {
+    const long long t = blockIdx.x * static_cast<long long>(kBlock) + threadIdx.x;
+    const long long step = static_cast<long long>(gridDim.x) * kBlock;
+    for (long long i = t; i < kAccTotal; i += step) {
+        const int q = static_cast<int>(i) - (6 + 4 * kWidthLists);
+        acc[i] = i == 0 ? preload : q >= 0 && q < 3 * kWidthLists && q % 3 == 1 ? ~0ull : 0ull;
+    }
+    for (int j = 0; j < c.jobs; j++)
+        for (long long i = t; i < c.n[j]; i += step) c.p[j][i] = c.v[j];
+}
+
 // Classify roots, run the light and heavy kernels of one traversal, and read
 // the results back.  `pivot_all` selects the pivot kernels (-1: graph
 // orientation, 0: pivot with target k, 1: pivot count-all, 2: pivot per-vertex
@@ -637,17 +625,15 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
     }
     const int nroots = ec ? d->m : d->n;
     const int dm = bit_dmax(d->d_max);   // the on-chip kernels never see a wide root
-    KC_CHECK(hipMemsetAsync(w.ctl, 0, CC_WORDS * sizeof(int), s));
-    unsigned long long init[kAccTotal] = {};
-    init[0] = preload;
-    for (int j = 0; j < kWidthLists; j++) init[6 + 4 * kWidthLists + 3 * j + 1] = ~0ull;   // min start of each list's timing
-    KC_CHECK(hipMemcpyAsync(w.acc, init, sizeof(init), hipMemcpyHostToDevice, s));
+    // everything that a launch expects cleared, in one launch
+    Clear clear;
+    clear.add(w.ctl, CC_WORDS, 0);
     if (pivot_all >= 0) {
-        KC_CHECK(hipMemsetAsync(w.counts, 0, 2 * sizeof(unsigned long long) * w.counts_len, s));
+        clear.add(w.counts, 4LL * w.counts_len, 0);
         // frame queues of the light, the heavy and the middle launch
-        KC_CHECK(hipMemsetAsync(w.qctl, 0, sizeof(int) * kQueueCtlTotal, s));
-        KC_CHECK(hipMemsetAsync(w.qready, 0, sizeof(int) * kQueueCap * 3, s));
-        KC_CHECK(hipMemsetAsync(w.leaves, 0, sizeof(unsigned long long) * w.leaf_count, s));
+        clear.add(w.qctl, kQueueCtlTotal, 0);
+        clear.add(w.qready, 3LL * kQueueCap, 0);
+        clear.add(w.leaves, 2LL * w.leaf_count, 0);
         int st0 = pivot_binom_table(w, s);
         if (st0 != KC_OK) return st0;
     }
@@ -667,22 +653,24 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         if (lane_lds_bytes(1 << top, k, ec, pair_list(k, ec, top)) > 160 * 1024) lane_path = false;
     }
     if (lane_path) {
-        KC_CHECK(hipMemsetAsync(w.active, 0xff, 2 * sizeof(int) * w.nactive, s));
         if (k >= (ec ? 3 : 2) + 4) {
-            KC_CHECK(hipMemsetAsync(w.task_ctr, 0, sizeof(int) * static_cast<size_t>(nroots), s));
-            KC_CHECK(hipMemsetAsync(w.task_tot, 0, sizeof(int) * static_cast<size_t>(nroots), s));
-            KC_CHECK(hipMemsetAsync(w.qctl, 0, sizeof(int) * kQueueCtlWords * kWidthLists, s));
-            KC_CHECK(hipMemsetAsync(w.qready, 0, sizeof(int) * kQueueCap * kQueueLists, s));
+            clear.add(w.active, 2LL * w.nactive, -1);
+            clear.add(w.task_ctr, nroots, 0);
+            clear.add(w.task_tot, nroots, 0);
+            clear.add(w.qctl, kQueueCtlWords * kWidthLists, 0);
+            clear.add(w.qready, static_cast<long long>(kQueueCap) * kQueueLists, 0);
         }
+    }
+    k_clear<<<clear.grid(), kBlock, 0, s>>>(clear, w.acc, preload);
+    KC_CHECK(hipGetLastError());
+    if (lane_path) {
         if (ec) {
             const int cap = dm > 1 ? dm : 1;
             int sblocks = div_up(d->n, kSizeWaves);
             if (sblocks > device_cus() * 8) sblocks = device_cus() * 8;
             if (sblocks < 1) sblocks = 1;
             k_sizes_ec<<<sblocks, 64 * kSizeWaves, kSizeWaves * cap * sizeof(int), s>>>(
-                d->n, need, d->row_ptr, d->col, d->src, w.heavy, w.ctl, cap);
-        } else {
-            k_classify_w<false, false><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.ctl, w.heavy);
+                d->n, need, d->row_ptr, d->col, d->src, w.heavy, cap);
         }
     } else if (ec) {
         k_classify<true><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.heavy, w.nroots_cap, mid_cap, w.ctl);
@@ -698,11 +686,9 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
     if (lane_path) {
         // lane walks over the width lists, widest first so that the largest roots
         // start early; profile: heavy = lists with >= 4 words, light = 1-2 words
-        if (ec)
-            k_classify_w<true, true><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.ctl, w.heavy);
-        else
-            k_classify_w<false, true><<<cblocks, kBlock, 0, s>>>(nroots, need, d->row_ptr, d->col, d->src, w.light, w.ctl, w.heavy);
-        KC_CHECK(hipGetLastError());
+        st = ec ? lists_launch_widths(EdgeLists{w.heavy}, nroots, w.bcnt, w.light, w.ctl, s)
+                : lists_launch_widths(VertexLists{need, d->row_ptr}, nroots, w.bcnt, w.light, w.ctl, s);
+        if (st != KC_OK) return st;
         if (prof) KC_CHECK(hipEventRecord(pe->ev[1], s));
         int top = 0;
         while (top < kWidthLists - 1 && (32 << top) < dm) top++;
@@ -876,9 +862,9 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         if (!lane_path && dm <= kLightCap) KC_CHECK(hipEventRecord(pe->ev[2], s));
         KC_CHECK(hipEventRecord(pe->ev[3], s));
     }
-    unsigned long long hacc[kAccTotal];
-    KC_CHECK(hipMemcpyAsync(hacc, w.acc, sizeof(hacc), hipMemcpyDeviceToHost, s));
-    KC_CHECK(hipMemcpyAsync(hctl, w.ctl, CC_WORDS * sizeof(int), hipMemcpyDeviceToHost, s));
+    // the control words and the accumulators are neighbours in the workspace
+    alignas(8) unsigned char hback[kAccAfterCtl + kAccTotal * sizeof(unsigned long long)];
+    KC_CHECK(hipMemcpyAsync(hback, w.ctl, sizeof(hback), hipMemcpyDeviceToHost, s));
     int hq[kQueueCtlWords * kWidthLists] = {};
     const bool queued = lane_path && k >= (ec ? 3 : 2) + 4;
     if (prof && queued)
@@ -887,6 +873,9 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         KC_CHECK(hipMemcpyAsync(counts_out, w.counts, 2 * sizeof(unsigned long long) * counts_len,
                                 hipMemcpyDeviceToHost, s));
     KC_CHECK(hipStreamSynchronize(s));
+    unsigned long long hacc[kAccTotal];
+    std::memcpy(hctl, hback, CC_WORDS * sizeof(int));
+    std::memcpy(hacc, hback + kAccAfterCtl, sizeof(hacc));
     std::copy(hacc, hacc + kAccWords, res);
     for (int j = 0; j < kAccSlots; j++) {
         const unsigned long long* x = hacc + kAccSlotBase + j * kAccSlotStride;

@@ -12,6 +12,7 @@ constexpr int kMidCap = 128;           // and of the pivot's middle list
 constexpr __host__ __device__ int leaf_index(int t, int nh) { return t * (t + 1) / 2 + nh; }
 constexpr int kPivBlocksPerCU = 8;     // grid cap of the heavy pivot kernel (sizes its stacks)
 constexpr int kLaneWavesPerCU = 32;    // grid cap of the lane-walk kernel (sizes its registry)
+constexpr int kListBlocks = 512;        // blocks that write the width lists
 constexpr int kWidthLists = 6;         // root lists by bitset words per row: 1, 2, 4, 8, 16, 32
 constexpr int kQueueCap = 16384;        // lane walk: ring slots for subtrees handed between wavefronts (power of 2)
 constexpr int kItemWords = 36;          // queue item: root slot, path length, 2 spare, 32 words of R
@@ -82,10 +83,11 @@ enum CountCtl {
     CC_MID_N = 7,        // pivot: middle root count
     CC_MID_HEAD = 14,    // pivot: middle queue head
     CC_WN0 = 8,          // width lists: root counts (8..13)
-    CC_WC0 = 16,         // width lists: fill cursors (16..21)
     CC_WH0 = 24,         // width lists: queue heads (24..29)
     CC_WORDS = 32
 };
+
+constexpr size_t kAccAfterCtl = 256;   // bytes from the control words to the accumulators
 
 // Saved levels a depth-first walk starting at path length `first` may need:
 // the last two levels of a path are counted in registers (a node one level
@@ -197,6 +199,7 @@ struct CountWs {
     int* task_ctr;                // lane walk, pair tasks: claimed tasks per root
     int* task_tot;                // lane walk, pair tasks: total tasks + 1 per root (0 = unpublished)
     int* active;                  // lane walk: root slot owned by each wavefront (-1 = none), main + side
+    int* bcnt;                    // width lists: roots per list and block
     int* qctl;                    // lane walk, subtree queue: kQueueCtlWords per width list
     int* qready;                  // subtree queue: slot sequence words, kQueueCap per queue (see queue_of)
     unsigned int* qitems;         // lane walk, subtree queue: kItemWords per slot, main + side
@@ -216,7 +219,7 @@ inline CountWs carve_count(void* ws, const kc_dag* d, bool pivot, size_t* bytes)
     CountWs w{};
     const int nr = d->m > d->n ? d->m : d->n;
     w.ctl = c.take<int>(CC_WORDS);
-    w.acc = c.take<unsigned long long>(kAccTotal);
+    w.acc = c.take<unsigned long long>(kAccTotal);      // kAccAfterCtl bytes after ctl
     w.light = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.heavy = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.nroots_cap = nr > 0 ? nr : 1;
@@ -224,6 +227,7 @@ inline CountWs carve_count(void* ws, const kc_dag* d, bool pivot, size_t* bytes)
     w.task_tot = c.take<int>(static_cast<size_t>(nr > 0 ? nr : 1));
     w.nactive = device_cus() * kLaneWavesPerCU;
     w.active = c.take<int>(2 * static_cast<size_t>(w.nactive));    // main and side stream
+    w.bcnt = c.take<int>(kWidthLists * kListBlocks);
     w.qctl = c.take<int>(kQueueCtlTotal);
     w.qready = c.take<int>(static_cast<size_t>(kQueueCap) * kQueueLists);
     w.qitems = c.take<unsigned int>(2 * static_cast<size_t>(kQueueCap) * kItemWords);   // main and side stream
