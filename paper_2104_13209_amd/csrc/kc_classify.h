@@ -17,11 +17,22 @@ __device__ __forceinline__ int width_list(int bound) {
     return bound <= 32 ? 0 : bound <= 64 ? 1 : bound <= 128 ? 2 : bound <= 256 ? 3 : bound <= 512 ? 4 : 5;
 }
 
-// First root of block b's share (a multiple of the roots of one step).
-__device__ __forceinline__ long long list_share(int nroots, int b) {
+// Roots of one block's share (a multiple of the roots of one step), and the blocks that
+// have any: the 2,000 roots of a small count are two blocks, not 512 that all add up
+// 512 counts per list.
+__host__ __device__ __forceinline__ long long list_per_block(int nroots) {
     const long long step = kListThreads * kListUnroll;
-    const long long per = ((static_cast<long long>(nroots) + kListBlocks - 1) / kListBlocks + step - 1) / step * step;
-    const long long at = per * b;
+    return ((static_cast<long long>(nroots) + kListBlocks - 1) / kListBlocks + step - 1) / step * step;
+}
+
+inline int list_blocks(int nroots) {
+    const long long per = list_per_block(nroots);
+    return nroots > 0 ? static_cast<int>((nroots + per - 1) / per) : 1;
+}
+
+// First root of block b's share.
+__device__ __forceinline__ long long list_share(int nroots, int b) {
+    const long long at = list_per_block(nroots) * b;
     return at < nroots ? at : nroots;
 }
 
@@ -61,7 +72,7 @@ __global__ void __launch_bounds__(kListThreads) k_lists_fill(ListOf list_of, int
 #pragma unroll
     for (int j = 0; j < kWidthLists; j++) {
         int before = 0, all = 0;
-        for (int b = threadIdx.x; b < kListBlocks; b += kListThreads) {
+        for (int b = threadIdx.x; b < static_cast<int>(gridDim.x); b += kListThreads) {
             const int x = bcnt[j * kListBlocks + b];
             all += x;
             before += b < static_cast<int>(blockIdx.x) ? x : 0;
@@ -118,8 +129,8 @@ __global__ void __launch_bounds__(kListThreads) k_lists_fill(ListOf list_of, int
 
 template <class ListOf>
 int lists_launch_widths(const ListOf& list_of, int nroots, int* bcnt, int* lists, int* ctl, hipStream_t s) {
-    k_lists_count<<<kListBlocks, kListThreads, 0, s>>>(list_of, nroots, bcnt);
-    k_lists_fill<<<kListBlocks, kListThreads, 0, s>>>(list_of, nroots, bcnt, lists, ctl);
+    k_lists_count<<<list_blocks(nroots), kListThreads, 0, s>>>(list_of, nroots, bcnt);
+    k_lists_fill<<<list_blocks(nroots), kListThreads, 0, s>>>(list_of, nroots, bcnt, lists, ctl);
     KC_CHECK(hipGetLastError());
     return KC_OK;
 }
