@@ -94,13 +94,18 @@ __device__ __forceinline__ void short_rows(int b, int e, int per, int lane, Step
 // shorter one of the two; rows hold no entry twice, so if also as many entries point
 // up as down, every up entry is the reverse of one of them.  That halves the
 // searches of testing every entry and keeps them out of the hubs' rows: 2,870 us on
-// the 1M-vertex power-law graph before.  Bound by the gathers of the searches.
+// the 1M-vertex power-law graph before, 1,280 so.  Down entries are gathered in LDS until
+// a wavefront has 64 of them, for half the lanes would idle in the search loops, and
+// searched with three probes a step: 1,170 us, bound by the gathers (16M rows of some
+// two lines each).
 __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per, int run, const int* __restrict__ row_ptr,
                                                        const int* __restrict__ col, int* ctl) {
     __shared__ long long s_up;
     __shared__ int s_bad;
     __shared__ LongRows longs;
+    __shared__ int s_find[kRowBlock / 64][3][128];    // searches put off until 64 are there: id, row's begin and end
     const int lane = threadIdx.x & 63;
+    int (*find)[128] = s_find[threadIdx.x >> 6];
     if (threadIdx.x == 0) {
         s_up = 0;
         s_bad = 0;
@@ -121,38 +126,71 @@ __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per,
         }
         if (e - b > kLongRow) longs.row[atomicAdd(&longs.n, 1)] = row;
     }
-    auto check = [&](int v, int dv, int first, int j) {
-        const int w = col[j];
-        if (w < 0 || w >= n || w == v) {
-            bad = 1;
-            return;
+    int left = 0;                                     // searches put off, below 64
+    auto search = [&](int at, bool in) {
+        int v = 0, lo = 0, hi = 0;
+        if (in) {
+            v = find[0][at];
+            lo = find[1][at];
+            hi = find[2][at];
         }
-        if (j > first && col[j - 1] >= w) bad = 1;
-        int lo = row_ptr[w], hi = row_ptr[w + 1];
-        lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
-        hi = hi < lo ? lo : (hi > nnz ? nnz : hi);
-        const int dw = hi - lo;
-        if (dw > dv || (dw == dv && w > v)) {
-            up++;
-            return;
+        bool hit = !in;
+        while (lo < hi) {                             // three probes a step: fewer loads in a chain
+            const int len = hi - lo;
+            const int p0 = lo + (len >> 2), p1 = lo + (len >> 1), p2 = p1 + (len >> 2);
+            const int x0 = col[p0], x1 = col[p1], x2 = col[p2];
+            hit |= x0 == v || x1 == v || x2 == v;
+            hi = x0 >= v ? p0 : x1 >= v ? p1 : x2 >= v ? p2 : hi;
+            lo = x2 < v ? p2 + 1 : x1 < v ? p1 + 1 : x0 < v ? p0 + 1 : lo;
+            if (hit) break;
         }
-        up--;
-        const int end = hi;
-        while (lo < hi) {
-            const int mid = lo + ((hi - lo) >> 1);
-            if (col[mid] < v) lo = mid + 1; else hi = mid;
+        if (!hit) bad = 1;
+    };
+    // all lanes of the wavefront together
+    auto check = [&](int v, int dv, int first, int j, bool in) {
+        int lo = 0, hi = 0;
+        bool down = false;
+        if (in) {
+            const int w = col[j];
+            if (w < 0 || w >= n || w == v) {
+                bad = 1;
+            } else {
+                if (j > first && col[j - 1] >= w) bad = 1;
+                lo = row_ptr[w];
+                hi = row_ptr[w + 1];
+                lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
+                hi = hi < lo ? lo : (hi > nnz ? nnz : hi);
+                const int dw = hi - lo;
+                down = !(dw > dv || (dw == dv && w > v));
+                up += down ? -1 : 1;
+            }
         }
-        if (lo >= end || col[lo] != v) bad = 1;
+        const unsigned long long m = __ballot(down);
+        if (down) {
+            const int at = left + __popcll(m & lanemask_lt());
+            find[0][at] = v;
+            find[1][at] = lo;
+            find[2][at] = hi;
+        }
+        left += __popcll(m);
+        if (left >= 64) {
+            wave_sync_lds();
+            left -= 64;
+            search(left + lane, true);
+            wave_sync_lds();
+        }
     };
     short_rows(b, e, per, lane, [&](int from, int first, int j, bool in) {
-        const int v = __shfl(row, from), dv = __shfl(e - b, from);
-        if (in) check(v, dv, first, j);
+        check(__shfl(row, from), __shfl(e - b, from), first, j, in);
     });
     __syncthreads();
     for (int l = 0; l < longs.n; l++) {
         const int v = longs.row[l], first = row_ptr[v], last = row_ptr[v + 1];
-        for (int j = first + threadIdx.x; j < last; j += kRowBlock) check(v, last - first, first, j);
+        for (int j = first + (threadIdx.x & ~63); j < last; j += kRowBlock)
+            check(v, last - first, first, j + lane, j + lane < last);
     }
+    wave_sync_lds();
+    search(lane, lane < left);
     up = wave_sum(up);
     if (lane == 0 && up) atomicAdd(reinterpret_cast<unsigned long long*>(&s_up), static_cast<unsigned long long>(up));
     if (bad) s_bad = 1;
