@@ -1147,7 +1147,7 @@ extern "C" KC_API int32_t kc_count_local(const kc_dag* d, int32_t k, int32_t piv
         if (st != KC_OK) return st;
     } else {
         const int st = local_orient_launch(d, k, scheme == KC_SCHEME_EC, reinterpret_cast<unsigned long long*>(local),
-                                           w.ctl, cancel, s);
+                                           w, cancel, s);
         if (st != KC_OK) return st;
         KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
         KC_CHECK(hipStreamSynchronize(s));
@@ -1169,7 +1169,7 @@ extern "C" KC_API int32_t kc_list(const kc_dag* d, int32_t k, int32_t* cliques, 
     if (!ws || ws_bytes < need) return KC_ENOMEM;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (k == 1 || k == 2) {
-        const int st = list_orient_launch(d, k, false, cliques, cap, nullptr, nullptr, nullptr, s);
+        const int st = list_orient_launch(d, k, false, cliques, cap, nullptr, w, nullptr, s);
         if (st != KC_OK) return st;
         KC_CHECK(hipStreamSynchronize(s));
         *total = k == 1 ? static_cast<uint64_t>(d->n) : static_cast<uint64_t>(d->m);
@@ -1180,7 +1180,7 @@ extern "C" KC_API int32_t kc_list(const kc_dag* d, int32_t k, int32_t* cliques, 
     const int* cancel = o ? const_cast<const int*>(reinterpret_cast<const volatile int*>(o->cancel)) : nullptr;
     KC_CHECK(hipMemsetAsync(w.ctl, 0, CC_WORDS * sizeof(int), s));
     KC_CHECK(hipMemsetAsync(w.acc, 0, sizeof(unsigned long long), s));
-    const int st = list_orient_launch(d, k, scheme == KC_SCHEME_EC, cliques, cap, w.acc, w.ctl, cancel, s);
+    const int st = list_orient_launch(d, k, scheme == KC_SCHEME_EC, cliques, cap, w.acc, w, cancel, s);
     if (st != KC_OK) return st;
     int hctl[CC_WORDS];
     unsigned long long listed = 0;

@@ -371,16 +371,15 @@ int go_batch_launch(const GoBatchLaunch& B, hipStream_t s);
 int lists_launch(const kc_dag* d, int k, bool ec, const CountWs& w, const int* cancel, hipStream_t s);
 
 // Per-vertex counts by graph orientation (kc_local.hip): zeroes `local` (n
-// entries, input ids) and adds every vertex's k-clique count; ctl is the
-// count workspace's control block (zero at launch).
-int local_orient_launch(const kc_dag* d, int k, bool ec, unsigned long long* local, int* ctl, const int* cancel,
-                        hipStream_t s);
+// entries, input ids) and adds every vertex's k-clique count; w.ctl is zero at launch.
+int local_orient_launch(const kc_dag* d, int k, bool ec, unsigned long long* local, const CountWs& w,
+                        const int* cancel, hipStream_t s);
 
 // k-clique listing by graph orientation (kc_local.hip): writes up to `cap` rows
 // of k input ids into `list` and counts every k-clique into *listed (device,
-// zero at launch); ctl is the count workspace's control block (zero at launch).
+// zero at launch); w.ctl is zero at launch.
 int list_orient_launch(const kc_dag* d, int k, bool ec, int* list, long long cap, unsigned long long* listed,
-                       int* ctl, const int* cancel, hipStream_t s);
+                       const CountWs& w, const int* cancel, hipStream_t s);
 
 // Capture-safe degree orientation (kc_orient.hip).
 size_t orient_async_workspace(int n, int nnz);

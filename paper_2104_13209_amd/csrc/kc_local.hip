@@ -16,16 +16,25 @@
 // leaf reserve consecutive rows of the caller's output with one atomic add per
 // lane, and every row below the capacity receives the clique's vertices (input
 // ids, ascending orientation rank: root vertices, path, member of I).
+#include "kc_classify.h"
 #include "kc_count_impl.h"
 #include "kc_extract.h"
 
 namespace kc {
 namespace {
 
+// Roots are claimed in width lists' order, widest first, in chunks this small: the time is
+// that of the largest roots, one wavefront each, and those claimed last were waited for.
+// Per-vertex k = 5 counts on a 200k-vertex power-law graph: 4.0 ms in id order in chunks of
+// 64, 2.8 ms so.  A launch per list and width lets more wavefronts in, but the lists' ends
+// add up: 7.4 ms.
+constexpr int kLocalChunk = 8;
+
 struct LocalParams {
     int k;
-    int nroots;
-    int need;                         // smallest |S| bound that can hold a k-clique
+    int need;                         // smallest |S| that can hold a k-clique
+    const int* __restrict__ lists;    // roots by size bound of S: width lists, back to back
+    const int* __restrict__ counts;   // root count of every list
     int s_cap;
     int levels;                       // saved levels per lane
     const int* __restrict__ row_ptr;
@@ -100,26 +109,12 @@ __global__ void __launch_bounds__(64) k_local(LocalParams P) {
     const int p0 = EC ? 3 : 2;                           // path length of a task's first node
     const unsigned long long lt = lanemask_lt();
 
+    int nroots = 0;
+    for (int j = 0; j < kWidthLists; j++) nroots += P.counts[j];
     RootClaims rc;
-    unsigned long long todo = 0;                         // bits: roots of the claimed chunk
     for (;;) {
-        if (todo == 0ull) {
-            if (!claim_chunk(rc, P.head, P.nroots, blockIdx.x, gridDim.x, 64)) break;
-            // the size bound of S decides before any extraction: a lane per root
-            int bound = -1;
-            if (lane < rc.left) {
-                const int r = rc.next + lane * rc.step;
-                if (EC) {
-                    const int u = P.src[r], v = P.col[r];
-                    const int du = P.row_ptr[u + 1] - P.row_ptr[u], dv = P.row_ptr[v + 1] - P.row_ptr[v];
-                    bound = du - 1 < dv ? du - 1 : dv;
-                } else {
-                    bound = P.row_ptr[r + 1] - P.row_ptr[r];
-                }
-            }
-            todo = __ballot(bound >= P.need && bound >= 0);
-            continue;
-        }
+        const int slot = claim_root(rc, P.head, nroots, blockIdx.x, gridDim.x, kLocalChunk);
+        if (slot < 0) break;
         if (P.cancel) {
             int c = 0;
             if (lane == 0 && cancel_requested(P.cancel)) {
@@ -128,8 +123,7 @@ __global__ void __launch_bounds__(64) k_local(LocalParams P) {
             }
             if (__shfl(c, 0)) break;
         }
-        const int root = rc.next + (__ffsll(static_cast<long long>(todo)) - 1) * rc.step;
-        todo &= todo - 1ull;
+        const int root = P.lists[nroots - 1 - slot];   // widest first
         extract_set<1, EC>(root, P.row_ptr, P.col, P.src, lane, S, &ctl[1]);
         const int s = ctl[1];
         if (s < P.need) continue;
@@ -318,13 +312,34 @@ int launch_local_t(const LocalParams& base, hipStream_t s) {
     return KC_OK;
 }
 
+// Lists of roots by the size bound of S.
+template <bool EC>
+struct LocalLists {
+    int need;
+    const int *row_ptr, *col, *src;
+    __device__ __forceinline__ int operator()(int r) const {
+        const int u = EC ? src[r] : r;
+        int bound = row_ptr[u + 1] - row_ptr[u];
+        if (EC) {
+            const int v = col[r];
+            const int dv = row_ptr[v + 1] - row_ptr[v];
+            bound = bound - 1 < dv ? bound - 1 : dv;
+        }
+        return bound < need || bound < 0 ? -1 : width_list(bound);
+    }
+};
+
 template <bool EC, bool LIST>
-int launch_local(const LocalParams& P, int d_max, hipStream_t s) {
-    if (d_max <= 32) return launch_local_t<1, EC, LIST>(P, s);
-    if (d_max <= 64) return launch_local_t<2, EC, LIST>(P, s);
-    if (d_max <= 128) return launch_local_t<4, EC, LIST>(P, s);
-    if (d_max <= 256) return launch_local_t<8, EC, LIST>(P, s);
-    if (d_max <= 512) return launch_local_t<16, EC, LIST>(P, s);
+int launch_local(const LocalParams& P, const kc_dag* d, const CountWs& w, hipStream_t s) {
+    const int nroots = EC ? d->m : d->n;
+    const int st = lists_launch_widths(LocalLists<EC>{P.need, d->row_ptr, d->col, d->src}, nroots, w.bcnt, w.light,
+                                       w.ctl, s);
+    if (st != KC_OK) return st;
+    if (d->d_max <= 32) return launch_local_t<1, EC, LIST>(P, s);
+    if (d->d_max <= 64) return launch_local_t<2, EC, LIST>(P, s);
+    if (d->d_max <= 128) return launch_local_t<4, EC, LIST>(P, s);
+    if (d->d_max <= 256) return launch_local_t<8, EC, LIST>(P, s);
+    if (d->d_max <= 512) return launch_local_t<16, EC, LIST>(P, s);
     return launch_local_t<32, EC, LIST>(P, s);
 }
 
@@ -345,8 +360,8 @@ __global__ void k_list_small(int k, int n, int m, const int* __restrict__ src, c
 
 }  // namespace
 
-int local_orient_launch(const kc_dag* d, int k, bool ec, unsigned long long* local, int* ctl, const int* cancel,
-                        hipStream_t s) {
+int local_orient_launch(const kc_dag* d, int k, bool ec, unsigned long long* local, const CountWs& w,
+                        const int* cancel, hipStream_t s) {
     const int n = d->n, m = d->m;
     const int grid = div_up(n > m ? n : m, 256) < device_cus() * 8 ? div_up(n > m ? n : m, 256) : device_cus() * 8;
     k_fill_local<<<grid > 0 ? grid : 1, 256, 0, s>>>(n, local, k == 1 ? 1ull : 0ull);
@@ -359,7 +374,6 @@ int local_orient_launch(const kc_dag* d, int k, bool ec, unsigned long long* loc
     }
     LocalParams P;
     P.k = k;
-    P.nroots = ec ? m : n;
     P.need = ec ? k - 2 : k - 1;
     P.s_cap = 0;
     // saved levels: the path grows from p0 to k - 1, one level per path length
@@ -369,18 +383,20 @@ int local_orient_launch(const kc_dag* d, int k, bool ec, unsigned long long* loc
     P.col = d->col;
     P.src = d->src;
     P.perm = d->perm;
-    P.head = ctl + CC_LIGHT_HEAD;
+    P.head = w.ctl + CC_LIGHT_HEAD;
+    P.lists = w.light;
+    P.counts = w.ctl + CC_WN0;
     P.local = local;
-    P.flags = ctl + CC_FLAGS;
+    P.flags = w.ctl + CC_FLAGS;
     P.cancel = cancel;
     P.list = nullptr;
     P.cap = 0;
     P.listed = nullptr;
-    return ec ? launch_local<true, false>(P, d->d_max, s) : launch_local<false, false>(P, d->d_max, s);
+    return ec ? launch_local<true, false>(P, d, w, s) : launch_local<false, false>(P, d, w, s);
 }
 
 int list_orient_launch(const kc_dag* d, int k, bool ec, int* list, long long cap, unsigned long long* listed,
-                       int* ctl, const int* cancel, hipStream_t s) {
+                       const CountWs& w, const int* cancel, hipStream_t s) {
     const int n = d->n, m = d->m;
     if (k <= 2) {
         const long long items = k == 1 ? n : m;
@@ -396,7 +412,6 @@ int list_orient_launch(const kc_dag* d, int k, bool ec, int* list, long long cap
     if (m == 0 || k > d->d_max + 1) return KC_OK;
     LocalParams P;
     P.k = k;
-    P.nroots = ec ? m : n;
     P.need = ec ? k - 2 : k - 1;
     P.s_cap = 0;
     const int p0 = ec ? 3 : 2;
@@ -405,14 +420,16 @@ int list_orient_launch(const kc_dag* d, int k, bool ec, int* list, long long cap
     P.col = d->col;
     P.src = d->src;
     P.perm = d->perm;
-    P.head = ctl + CC_LIGHT_HEAD;
+    P.head = w.ctl + CC_LIGHT_HEAD;
+    P.lists = w.light;
+    P.counts = w.ctl + CC_WN0;
     P.local = nullptr;
-    P.flags = ctl + CC_FLAGS;
+    P.flags = w.ctl + CC_FLAGS;
     P.cancel = cancel;
     P.list = list;
     P.cap = cap;
     P.listed = listed;
-    return ec ? launch_local<true, true>(P, d->d_max, s) : launch_local<false, true>(P, d->d_max, s);
+    return ec ? launch_local<true, true>(P, d, w, s) : launch_local<false, true>(P, d, w, s);
 }
 
 }  // namespace kc

@@ -60,3 +60,21 @@ def test_batch_of_cliques(kc):
         for k in (3, 4):
             want = [math.comb(33, k), 0, sum(math.comb(c, k) for c in (65, 66, 129)), 0, math.comb(258, k)]
             assert kc.batch_count(kc.batch_to_device(b), k, plan) == want, k
+
+
+@pytest.mark.parametrize("n", [514, 1025, 2049, 524289])
+def test_local_counts_and_lists(kc, n):
+    # d_max 513 would not fit a wavefront's LDS: sizes up to 258
+    sizes = [258] if n == 514 else BORDERS
+    g = cliques(n, sizes)
+    d = kc.orient(kc.to_device(g), kc.ORDER_DEGREE)
+    deg = g.degrees()
+    for scheme in (kc.SCHEME_VC, kc.SCHEME_EC):
+        for k in (3, 4):
+            want = [math.comb(x, k - 1) for x in range(258)]
+            got = kc.count_local(d, k, scheme=scheme).cpu().numpy()
+            assert np.array_equal(got, np.array(want)[deg]), k
+        total, rows = kc.list_cliques(d, 3, scheme=scheme)
+        rows = np.sort(rows.cpu().numpy().astype(np.int64), axis=1)
+        assert total == rows.shape[0] == sum(math.comb(c, 3) for c in sizes)
+        assert np.unique((rows[:, 0] * n + rows[:, 1]) * n + rows[:, 2]).size == total

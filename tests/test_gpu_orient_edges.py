@@ -63,3 +63,23 @@ def test_missing_reverse_entries_are_found_in_both_directions(kc, hub):
             with pytest.raises(kc.KcError) as e:
                 kc.orient(bad, order)
             assert e.value.code == kc.EINVAL
+
+
+@pytest.mark.parametrize("h", [1, 2, 3, 4, 5, 8, 16, 31, 32, 33, 127, 128, 129])
+def test_one_wrong_entry_is_found_at_any_place_of_a_row(kc, h):
+    # rows of 2h entries of one length (256: rows of a wavefront, longer: of the block); the
+    # wrong entry keeps the row sorted, and as many entries as before point up and down
+    import torch
+    n = 4 * h + 301
+    off = np.concatenate([-2 * np.arange(h, 0, -1), 2 * np.arange(1, h + 1)])
+    col = np.sort((np.arange(n)[:, None] + off[None, :]) % n, axis=1).astype(np.int32)
+    rp = torch.as_tensor(np.arange(n + 1, dtype=np.int32) * 2 * h).cuda()
+    assert kc.orient(kc.Csr(n, rp, torch.as_tensor(col.reshape(-1)).cuda()), kc.ORDER_DEGREE).m == n * h
+    for v in (2 * h, 2 * h + 77, n - 2 * h - 2):
+        for at in sorted({0, h // 2, h - 1, h, h + h // 2, 2 * h - 1}):
+            wrong = col.copy()
+            wrong[v, at] += 1
+            bad = kc.Csr(n, rp, torch.as_tensor(wrong.reshape(-1)).cuda())
+            with pytest.raises(kc.KcError) as e:
+                kc.orient(bad, kc.ORDER_DEGREE)
+            assert e.value.code == kc.EINVAL, (v, at)
