@@ -340,7 +340,7 @@ def bench_densecore(kc, reps):
                      "matches_oracle_counts": (got[:omega + 1] == [fixture.get(k) for k in range(omega + 1)])
                      if fixture else None,
                      "launch_ms": [round(x, 3) for x in launch_ms],
-                     "roofline": {"bound": "alu", "kernel": "k_piv (%s roots, count-all)" % ("light", "heavy")[j],
+                     "roofline": {"bound": "alu", "kernel": "k_piv_reg (%s roots, count-all)" % ("light", "heavy")[j],
                                   "achieved": round(achieved, 4), "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s",
                                   "frac": round(achieved / VALU_PEAK_TOPS, 5),
                                   "work": "2 int32 ops per bitset word: %d tree nodes reading %d words (scoring "

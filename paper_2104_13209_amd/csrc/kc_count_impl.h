@@ -17,7 +17,7 @@ constexpr int kWidthLists = 6;         // root lists by bitset words per row: 1,
 constexpr int kQueueCap = 16384;        // lane walk: ring slots for subtrees handed between wavefronts (power of 2)
 constexpr int kItemWords = 36;          // queue item: root slot, path length, 2 spare, 32 words of R
 // The lane walk's list 0 has no pair tasks and so no queue; list j >= 1 uses queue
-// j - 1, and the pivot launches use queues 0 (light) and 1 (heavy).
+// j - 1, and the pivot launches of kc_pivot.hip use queues 0 (light) and 1 (heavy).
 constexpr int kQueueLists = kWidthLists - 1;
 constexpr int queue_of(int list) { return list > 0 ? list - 1 : 0; }
 constexpr int kQueueCtlWords = 8;       // per width list: head, tail, pending, rooting, hungry

@@ -23,6 +23,8 @@
 // All control flow is wave-uniform; lane w holds word w of I, P and P-remaining.
 // The explicit stack lives in LDS for light roots (|S| <= 64) and in a per-
 // wavefront global-memory slab for heavy roots (its depth can reach |S|).
+// Totals of roots of at most 128 candidates run in kc_pivot_reg.hip instead; here
+// are those of larger roots, and the per-vertex counts of all.
 #include "kc_count_impl.h"
 #include "kc_extract.h"
 
