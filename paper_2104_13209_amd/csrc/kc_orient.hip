@@ -590,7 +590,9 @@ __global__ void __launch_bounds__(kBlock) k_core_rows(const int* __restrict__ ro
                 pos += __popcll(m);
             }
         }
-        if (pos + lane < end) rows[pos + lane] = static_cast<unsigned short>(kCoreCap);
+        // at most three slots on a symmetric graph; one that lacks reverse entries (and was not
+        // validated) can leave any number of them without a neighbour
+        for (int at = pos + lane; at < end; at += 64) rows[at] = static_cast<unsigned short>(kCoreCap);
     }
 }
 
@@ -619,8 +621,8 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_peel(const int2* __restrict
         s_min = INT_MAX;
     }
     __syncthreads();
-    // every vertex is queued once; the bound only matters for malformed graphs that
-    // the caller chose not to have validated
+    // every vertex is queued once: its degree falls to the level once, and starts a level
+    // at it once.  The bound costs nothing and does not rest on that.
     auto push = [&](int v) {
         const int at = atomicAdd(&s_tail, 1);
         if (at < kCoreCap) queue[at] = static_cast<unsigned short>(v);

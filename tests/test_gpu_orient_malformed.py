@@ -1,0 +1,56 @@
+"""Graphs without reverse entries, given with validate=False: the DAG is unspecified and the
+call may refuse it, but every access stays in the caller's arrays."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 4096
+
+
+def directed(kc, n, edges):
+    """The CSR with exactly these directed edges."""
+    import torch
+    e = np.unique(edges[:, 0].astype(np.int64) * n + edges[:, 1])
+    rp = np.concatenate([[0], np.cumsum(np.bincount(e // n, minlength=n))]).astype(np.int32)
+    return kc.Csr(n, torch.as_tensor(rp).cuda(), torch.as_tensor((e % n).astype(np.int32)).cuda())
+
+
+def both(a, b):
+    return np.concatenate([np.stack([a, b], 1), np.stack([b, a], 1)])
+
+
+def orient_guarded(kc, g, order):
+    """Status of the call; arrays and workspace (full of stale words) must end as they began."""
+    import torch
+    m = g.nnz // 2
+
+    def guarded(count):
+        return torch.full((count + GUARD,), -7, dtype=torch.int32, device="cuda")
+
+    out = kc.Dag(g.n, m, 0, -1, order, guarded(g.n + 1), guarded(m), guarded(m), guarded(g.n))
+    need = kc.orient_workspace_bytes(g.n, g.nnz, order)
+    ws = torch.full((need + GUARD,), 255, dtype=torch.uint8, device="cuda")
+    status = kc.OK
+    try:
+        kc.orient(g, order, validate=False, ws=ws[:need], out=out)
+    except kc.KcError as e:
+        status = e.code
+    torch.cuda.synchronize()
+    for t, count in ((out.row_ptr, g.n + 1), (out.col, m), (out.src, m), (out.perm, g.n)):
+        assert bool((t[count:] == -7).all())
+    assert bool((ws[need:] == 255).all())
+    return status
+
+
+@pytest.mark.parametrize("fan", [63, 64, 65, 66, 300, 1500])
+def test_peel_with_neighbours_that_left_without_a_reverse_entry(kc, fan):
+    # 1500 vertices without entries leave first, a path of 3000 takes 1500 rounds (so that the
+    # whole-device rounds end early), and 100 vertices list `fan` of the first 1500
+    rng = np.random.default_rng(fan)
+    path = np.arange(1500, 4499)
+    hub = np.arange(4500, 4600)
+    one_way = np.concatenate([np.stack([np.full(fan, h), rng.permutation(1500)[:fan]], 1) for h in hub])
+    e = np.concatenate([both(path, path + 1), one_way])
+    g = directed(kc, 4600, e)
+    assert orient_guarded(kc, g, kc.ORDER_DEGENERACY) == kc.EINVAL
