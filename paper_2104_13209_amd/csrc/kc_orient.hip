@@ -1234,20 +1234,22 @@ __global__ void __launch_bounds__(kRowBlock) k_outdeg(int n, int per, int run, c
 // of up to kLongRow neighbours of which at most kGroupRow are kept are handled by 16
 // lanes, the others by the whole block.  Rows of more than kRowCap kept neighbours
 // go to tmp[] unsorted and are finished by k_sort_long_rows.  Bound by the gathers of ranks.
+// Nothing is written when the rows hold more than `room` entries, which happens only on a
+// graph that lacks reverse entries (and was not validated).
 constexpr int kGroupRow = 64;
 
 __global__ void __launch_bounds__(kRowBlock) k_fill(int n, int per, int run, const int* __restrict__ row_ptr,
                                                    const int* __restrict__ col, const int* __restrict__ perm,
                                                    const int* __restrict__ rank,
                                                    const int* __restrict__ dag_ptr, int* dag_col, int* dag_src,
-                                                   int* tmp, int* ctl) {
+                                                   int* tmp, int room, int* ctl) {
     // a group's rows lie 16 words further apart than they are long, so that the four
     // broadcasts of a step use different banks
     __shared__ __align__(16) int groups[kRowBlock / 16][kGroupRow + 16];
     __shared__ __align__(16) int big_row[kRowCap + 4];
     __shared__ LongRows longs;
     __shared__ int s_pos;
-    if (rejected(ctl)) return;
+    if (rejected(ctl) || ctl[CTL_TOTAL] > room) return;
     const int lane = threadIdx.x & 63;
     const int g = lane >> 4, gl = lane & 15;
     int* grow = groups[threadIdx.x >> 4];
@@ -1476,10 +1478,10 @@ int exclusive_scan(int count, const int* in, int* out, int* tiles, int* ctl, hip
 }
 
 // Sort by key (key_a / val_a hold the keys and ids, CTL_MAXKEY the largest key, which
-// is at most `bound`), then out: perm, rank, and the DAG's rows.  Nothing is read on
-// the host.
+// is at most `bound`), then out: perm, rank, and the DAG's rows, of at most `room` entries.
+// Nothing is read on the host.
 int build_dag(const OrientWs& w, int n, int nnz, const int* row_ptr, const int* col, long long bound, bool grouped,
-              int* out_row_ptr, int* out_col, int* out_src, int* out_perm, hipStream_t s) {
+              int room, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, hipStream_t s) {
     const int ntiles = div_up(n, kTile);
     const RadixBuf rb{w.key_a, w.val_a, w.key_b, w.val_b};
     const int per = rows_per_wave(n), rows_grid = div_up(n, 16 * per);
@@ -1497,7 +1499,7 @@ int build_dag(const OrientWs& w, int n, int nnz, const int* row_ptr, const int* 
     if (st != KC_OK) return st;
     if (nnz > 0) {
         k_fill<<<rows_grid, kRowBlock, 0, s>>>(n, per, run, row_ptr, col, out_perm, w.rank, out_row_ptr, out_col, out_src,
-                                              w.tmp, w.ctl);
+                                              w.tmp, room, w.ctl);
         KC_CHECK(hipGetLastError());
     }
     return KC_OK;
@@ -1532,8 +1534,8 @@ int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, cons
     k_zero<<<1, kBlock, 0, s>>>(w.ctl, CTL_WORDS);
     k_degree_key<<<grid_for_keys(n), kBlock, 0, s>>>(n, row_ptr, w.key_a, w.val_a, w.ctl, *grouped ? voff : nullptr,
                                                     ngraphs, static_cast<int>(span));
-    int st = build_dag(w, n, nnz, row_ptr, col, *grouped ? keys - 1 : span - 1, *grouped, out_row_ptr, out_col,
-                       out_src, out_perm, s);
+    int st = build_dag(w, n, nnz, row_ptr, col, *grouped ? keys - 1 : span - 1, *grouped, INT_MAX, out_row_ptr,
+                       out_col, out_src, out_perm, s);
     if (st != KC_OK) return st;
     if (nnz > 0) {
         k_sort_long_rows<<<grid_for_threads(n), kBlock, 0, s>>>(n, out_row_ptr, w.tmp, out_col, out_src, w.ctl);
@@ -1687,7 +1689,8 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
     // 2. stable radix sort (key, id) -> position = new id; 3. filter: out-degrees and
     // their scan -> row_ptr; 4. compact + per-row sort.  Degrees and colours are below
     // n; the peel's rounds below 2 n, as a level change counts as one.
-    int st = build_dag(w, n, nnz, g->row_ptr, g->col, order == KC_ORDER_DEGENERACY ? 2LL * n : n, false, out->row_ptr, out->col, out->src, out->perm, s);
+    int st = build_dag(w, n, nnz, g->row_ptr, g->col, order == KC_ORDER_DEGENERACY ? 2LL * n : n, false, m,
+                       out->row_ptr, out->col, out->src, out->perm, s);
     if (st != KC_OK) return st;
     KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
     KC_CHECK(hipStreamSynchronize(s));

@@ -54,3 +54,18 @@ def test_peel_with_neighbours_that_left_without_a_reverse_entry(kc, fan):
     e = np.concatenate([both(path, path + 1), one_way])
     g = directed(kc, 4600, e)
     assert orient_guarded(kc, g, kc.ORDER_DEGENERACY) == kc.EINVAL
+
+
+@pytest.mark.parametrize("order", [0, 1, 3])
+@pytest.mark.parametrize("fan", [20, 200, 1300])
+def test_more_entries_kept_than_the_arrays_hold(kc, order, fan):
+    # 1000 vertices list `fan` of 1400 that list only one another: almost every entry points
+    # to the later end of its edge, twice as many as m
+    rng = np.random.default_rng(fan)
+    i, j = np.triu_indices(1400, 1)
+    near = (j - i) <= fan                          # rows of the 1400 longer than `fan`
+    one_way = np.concatenate([np.stack([np.full(fan, 1400 + v), rng.permutation(1400)[:fan]], 1) for v in range(1000)])
+    g = directed(kc, 2400, np.concatenate([both(i[near], j[near]), one_way]))
+    status = orient_guarded(kc, g, order)
+    if order == kc.ORDER_DEGREE:
+        assert status == kc.EINVAL
