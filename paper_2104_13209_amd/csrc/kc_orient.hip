@@ -744,7 +744,8 @@ __device__ int block_exclusive_scan(int x, int* total, int* sh /* >= kBlock/64 +
 // of degree at most 1.1 D / L (10 deg L <= 11 D, exact in integers) leaves in
 // round r; afterwards its remaining neighbours lose one degree each.  The round
 // is the sort key, ties by id.  Rounds end when no vertex is left (each removes
-// at least one: the smallest degree is at most the average).
+// at least one: the smallest degree is at most the average, unless missing reverse
+// entries have made the average negative).
 
 __global__ void __launch_bounds__(kBlock) k_ad_init(int n, const int* __restrict__ row_ptr, int* deg, int* rnd,
                                                    int* val) {
@@ -1637,7 +1638,7 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
         int* deg = w.key_b;   // scratch until the sort
         k_ad_init<<<grid_for_threads(n), kBlock, 0, s>>>(n, g->row_ptr, deg, w.rnd, w.val_a);
         KC_CHECK(hipGetLastError());
-        int r = 0;
+        int r = 0, before = -1;
         for (;; r++) {
             KC_CHECK(hipMemsetAsync(w.ctl + CTL_AD_LIVE, 0, 4 * sizeof(int), s));
             k_ad_sum<<<grid_for_threads(n), kBlock, 0, s>>>(n, deg, w.rnd, w.ctl);
@@ -1646,6 +1647,8 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
             KC_CHECK(hipMemcpyAsync(&live, w.ctl + CTL_AD_LIVE, sizeof(int), hipMemcpyDeviceToHost, s));
             KC_CHECK(hipStreamSynchronize(s));
             if (live == 0) break;
+            if (live == before) return KC_EINVAL;   // not symmetric (only possible without validation)
+            before = live;
             k_ad_mark<<<grid_for_threads(n), kBlock, 0, s>>>(n, r, deg, w.rnd, w.ctl);
             k_ad_dec<<<grid_for_waves(n), kBlock, 0, s>>>(n, r, g->row_ptr, g->col, deg, w.rnd);
             KC_CHECK(hipGetLastError());

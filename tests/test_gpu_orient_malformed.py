@@ -69,3 +69,15 @@ def test_more_entries_kept_than_the_arrays_hold(kc, order, fan):
     status = orient_guarded(kc, g, order)
     if order == kc.ORDER_DEGREE:
         assert status == kc.EINVAL
+
+
+@pytest.mark.parametrize("fan", [20, 200])
+def test_approximate_rounds_end_when_none_can_leave(kc, fan):
+    # the 1400 lose `fan` degrees to each of 1000 vertices that they do not list: their degrees
+    # sum to less than zero, and none is at most 1.1 times that average
+    rng = np.random.default_rng(fan)
+    i, j = np.triu_indices(1400, 1)
+    near = (j - i) <= fan
+    one_way = np.concatenate([np.stack([np.full(fan, 1400 + v), rng.permutation(1400)[:fan]], 1) for v in range(1000)])
+    g = directed(kc, 2400, np.concatenate([both(i[near], j[near]), one_way]))
+    assert orient_guarded(kc, g, kc.ORDER_APPROX_DEGENERACY) == kc.EINVAL
