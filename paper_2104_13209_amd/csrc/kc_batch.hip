@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(kBlock) k_fill_u64(unsigned long long* p, unsi
 __global__ void __launch_bounds__(kBlock) k_gid(int n, const int* __restrict__ perm, const int* __restrict__ voff,
                                                int ngraphs, int* gid) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int v = perm ? perm[i] : i;
+        const int v = perm[i];
         int lo = 0, hi = ngraphs;                        // voff[lo] <= v < voff[hi]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -189,12 +189,10 @@ extern "C" KC_API int32_t kc_batch_count(const kc_batch* b, int32_t k, uint64_t*
     }
     k_fill_u64<<<grid_for(2LL * G), kBlock, 0, s>>>(reinterpret_cast<unsigned long long*>(counts), 0ull, 2LL * G);
     const int n = b->n, m = b->nnz / 2;
-    bool grouped = false;
     int st = orient_degree_async(n, b->nnz, b->row_ptr, b->col, b->voff, G, b->max_degree, w.dag_row_ptr, w.dag_col,
-                                 w.dag_src, w.perm, w.orient_ws, s, &grouped);
+                                 w.dag_src, w.perm, w.orient_ws, s);
     if (st != KC_OK) return st;
-    // a grouped order keeps every graph's range of ids
-    k_gid<<<grid_for(n), kBlock, 0, s>>>(n, grouped ? nullptr : w.perm, b->voff, G, w.gid);
+    k_gid<<<grid_for(n), kBlock, 0, s>>>(n, w.perm, b->voff, G, w.gid);
     k_graph_bucket<<<grid_for(G), kBlock, 0, s>>>(G, b->voff, pl, w.bucket);
     k_fill_i32<<<grid_for(w.nactive), kBlock, 0, s>>>(w.active, -1, w.nactive);
     k_fill_u64<<<1, kBlock, 0, s>>>(w.acc, 0ull, kAccTotal);

@@ -385,7 +385,7 @@ int list_orient_launch(const kc_dag* d, int k, bool ec, int* list, long long cap
 size_t orient_async_workspace(int n, int nnz);
 int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, const int* voff, int ngraphs,
                         int max_degree, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, void* ws,
-                        hipStream_t s, bool* grouped);
+                        hipStream_t s);
 
 // Whether a width list runs by pair tasks: trees four levels deep from the second
 // vertex task on (shallower ones are counted from vertex tasks), except that roots of

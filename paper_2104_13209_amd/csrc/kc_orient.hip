@@ -1163,10 +1163,12 @@ __global__ void __launch_bounds__(kBlock) k_radix_scatter(int count, int pass, R
 
 // --------------------------------------------------------- filter, compact
 
-// perm = the sorted ids, rank = its inverse.
-__global__ void __launch_bounds__(kBlock) k_rank(int n, RadixBuf rb, int* perm, int* rank, const int* ctl) {
+// perm = the sorted ids, rank = its inverse.  `passes` were launched: fewer than the largest
+// key has digits where the caller's bound on the degrees is too low, and then that many ran.
+__global__ void __launch_bounds__(kBlock) k_rank(int n, int passes, RadixBuf rb, int* perm, int* rank, const int* ctl) {
     if (rejected(ctl)) return;
-    const int* val = (radix_passes(ctl) & 1) ? rb.val_b : rb.val_a;
+    const int ran = radix_passes(ctl) < passes ? radix_passes(ctl) : passes;
+    const int* val = (ran & 1) ? rb.val_b : rb.val_a;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int v = val[i];
         perm[i] = v;
@@ -1488,12 +1490,13 @@ int build_dag(const OrientWs& w, int n, int nnz, const int* row_ptr, const int* 
     const int per = rows_per_wave(n), rows_grid = div_up(n, 16 * per);
     const int run = grouped ? 16 * per : kRowRun;
     int *dtot = w.tiles, *hist = w.tiles + 256;
-    for (int pass = 0; pass < 4 && (bound >> (8 * pass)) != 0; pass++) {
+    int pass = 0;
+    for (; pass < 4 && (bound >> (8 * pass)) != 0; pass++) {
         k_radix_hist<<<ntiles, kBlock, 0, s>>>(n, pass, rb, hist, w.ctl);
         k_radix_scan<<<256, kBlock, 0, s>>>(ntiles, pass, hist, dtot, w.ctl);
         k_radix_scatter<<<ntiles, kBlock, 0, s>>>(n, pass, rb, hist, dtot, w.ctl);
     }
-    k_rank<<<grid_for_threads(n), kBlock, 0, s>>>(n, rb, out_perm, w.rank, w.ctl);
+    k_rank<<<grid_for_threads(n), kBlock, 0, s>>>(n, pass, rb, out_perm, w.rank, w.ctl);
     k_outdeg<<<rows_grid, kRowBlock, 0, s>>>(n, per, run, row_ptr, col, out_perm, w.rank, w.outdeg, w.ctl);
     KC_CHECK(hipGetLastError());
     const int st = exclusive_scan(n, w.outdeg, out_row_ptr, w.tiles, w.ctl, s);
@@ -1522,20 +1525,21 @@ size_t orient_async_workspace(int n, int nnz) {
 // so it can be captured in a HIP graph.  The vertices of a graph stay together (their
 // rows, ranks and roots share cache lines), ordered by (degree, id) inside it, unless
 // graph and degree do not fit one 31-bit key: then the union is ordered by degree.
-// Writes row_ptr, col, src, perm; returns through *grouped whether graphs stay together.
+// Writes row_ptr, col, src, perm.  The order is a permutation whatever max_degree says; one
+// that is too low lets graphs' ids mix, so the graph of an id is that of perm[id].
 int orient_degree_async(int n, int nnz, const int* row_ptr, const int* col, const int* voff, int ngraphs,
                         int max_degree, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, void* ws,
-                        hipStream_t s, bool* grouped) {
+                        hipStream_t s) {
     size_t need = 0;
     OrientWs w = carve(ws, n, nnz, &need);
     if (n <= 0) return KC_EINVAL;
     const long long span = static_cast<long long>(max_degree) + 1;
     const long long keys = span * ngraphs;
-    *grouped = keys <= INT_MAX;
+    const bool grouped = keys <= INT_MAX;
     k_zero<<<1, kBlock, 0, s>>>(w.ctl, CTL_WORDS);
-    k_degree_key<<<grid_for_keys(n), kBlock, 0, s>>>(n, row_ptr, w.key_a, w.val_a, w.ctl, *grouped ? voff : nullptr,
+    k_degree_key<<<grid_for_keys(n), kBlock, 0, s>>>(n, row_ptr, w.key_a, w.val_a, w.ctl, grouped ? voff : nullptr,
                                                     ngraphs, static_cast<int>(span));
-    int st = build_dag(w, n, nnz, row_ptr, col, *grouped ? keys - 1 : span - 1, *grouped, INT_MAX, out_row_ptr,
+    int st = build_dag(w, n, nnz, row_ptr, col, grouped ? keys - 1 : span - 1, grouped, INT_MAX, out_row_ptr,
                        out_col, out_src, out_perm, s);
     if (st != KC_OK) return st;
     if (nnz > 0) {
