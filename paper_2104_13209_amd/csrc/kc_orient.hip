@@ -11,7 +11,6 @@
 //             histogram, exclusive scan -> row_ptr (the paper's histogram + scan)
 //   compact   gather each kept row, sort it by new id, write col and the COO src
 #include <climits>
-#include <cstring>
 
 #include "kc_internal.h"
 
@@ -43,7 +42,7 @@ enum Ctl {
     CTL_AD_LIVE = 16,  // approximate degeneracy: vertices left
     CTL_AD_SUM = 18,   // approximate degeneracy: their degree sum (u64 over words 18, 19)
     CTL_BAR = 32,      // peel: barrier arrivals, on a cache line of their own
-    CTL_UP = 34,       // validation: entries to longer rows less those to shorter ones (i64 over words 34, 35)
+    CTL_UP = 34,       // validation: entries to longer rows less those to shorter ones (at most nnz < 2^31)
     CTL_WORDS = 64
 };
 
@@ -100,7 +99,7 @@ __device__ __forceinline__ void short_rows(int b, int e, int per, int lane, Step
 // two lines each).
 __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per, int run, const int* __restrict__ row_ptr,
                                                        const int* __restrict__ col, int* ctl) {
-    __shared__ long long s_up;
+    __shared__ int s_up;
     __shared__ int s_bad;
     __shared__ LongRows longs;
     __shared__ int s_find[kRowBlock / 64][3][128];    // searches put off until 64 are there: id, row's begin and end
@@ -113,7 +112,7 @@ __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per,
     }
     __syncthreads();
     int bad = 0;
-    long long up = 0;                                 // entries that point up, less those that point down
+    int up = 0;                                       // entries that point up, less those that point down
     const int row = block_row(n, per, run);
     int b = 0, e = 0;
     if (row >= 0) {
@@ -192,18 +191,18 @@ __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per,
     wave_sync_lds();
     search(lane, lane < left);
     up = wave_sum(up);
-    if (lane == 0 && up) atomicAdd(reinterpret_cast<unsigned long long*>(&s_up), static_cast<unsigned long long>(up));
+    if (lane == 0 && up) atomicAdd(&s_up, up);
     if (bad) s_bad = 1;
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (s_up) atomicAdd(reinterpret_cast<unsigned long long*>(ctl + CTL_UP), static_cast<unsigned long long>(s_up));
+        if (s_up) atomicAdd(&ctl[CTL_UP], s_up);
         if (s_bad) atomicOr(&ctl[CTL_BAD], 1);
     }
 }
 
 // An invalid graph: nothing after the validation may follow its indices.
 __device__ __forceinline__ bool rejected(const int* ctl) {
-    return ctl[CTL_BAD] != 0 || *reinterpret_cast<const long long*>(ctl + CTL_UP) != 0;
+    return ctl[CTL_BAD] != 0 || ctl[CTL_UP] != 0;
 }
 
 // --------------------------------------------------------------- keys
@@ -511,9 +510,17 @@ __global__ void __launch_bounds__(kBlock) k_peel_init(int n, const int* __restri
 // Local ids of the vertices left (cid[v], -1 for the others; list[id] = v) and
 // where their rows start among the compacted ones.  Ids and rows are handed out
 // block by block in any order: only the queue's order depends on it, and the keys
-// do not.  span[id] = {start, live degree}.
+// do not.  span[id] = {start, live degree}.  Both are read eight bytes at a time, but as
+// pairs of words: a caller's workspace need only be aligned to words.
+struct CoreSpan {
+    int at, degree;
+};
+struct CoreIds {
+    unsigned int ab, cd;   // four 16-bit ids
+};
+
 __global__ void __launch_bounds__(kPeelBlock) k_core_list(int n, const int* __restrict__ key,
-                                                         const int* __restrict__ deg, int* cid, int* list, int2* span,
+                                                         const int* __restrict__ deg, int* cid, int* list, CoreSpan* span,
                                                          int* ctl) {
     __shared__ int cnt[kPeelBlock / 64], sum[kPeelBlock / 64];
     __shared__ int base_id, base_at;
@@ -522,7 +529,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_list(int n, const int* __re
     const int v = blockIdx.x * kPeelBlock + threadIdx.x;
     const bool live = v < n && key[v] < 0;
     const int d = live && deg[v] > 0 ? deg[v] : 0;
-    const int room = (d + 3) & ~3;               // rows start at 8-byte boundaries
+    const int room = (d + 3) & ~3;               // four ids a load
     const unsigned long long m = __ballot(live);
     int inc = room;
 #pragma unroll
@@ -553,7 +560,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_list(int n, const int* __re
         id = base_id + cnt[w] + __popcll(m & lanemask_lt());
         if (id < kCoreCap) {
             list[id] = v;
-            span[id] = make_int2(base_at + sum[w] + inc - room, d);
+            span[id] = CoreSpan{base_at + sum[w] + inc - room, d};
         } else {
             id = -1;
         }
@@ -565,7 +572,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_list(int n, const int* __re
 // filled up to a multiple of four with the id kCoreCap, which stands for no vertex.
 __global__ void __launch_bounds__(kBlock) k_core_rows(const int* __restrict__ row_ptr,
                                                      const int* __restrict__ col, const int* __restrict__ cid,
-                                                     const int* __restrict__ list, const int2* __restrict__ span,
+                                                     const int* __restrict__ list, const CoreSpan* __restrict__ span,
                                                      unsigned short* rows, const int* ctl) {
     const int lane = threadIdx.x & 63;
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
@@ -574,8 +581,8 @@ __global__ void __launch_bounds__(kBlock) k_core_rows(const int* __restrict__ ro
     for (int i = wave; i < L; i += nwaves) {
         const int v = list[i];
         const int b = row_ptr[v], e = row_ptr[v + 1];
-        int pos = span[i].x;
-        const int end = pos + ((span[i].y + 3) & ~3);
+        int pos = span[i].at;
+        const int end = pos + ((span[i].degree + 3) & ~3);
         for (int j0 = b; j0 < e; j0 += 256) {
             int x[4], id[4];
 #pragma unroll
@@ -602,7 +609,7 @@ __global__ void __launch_bounds__(kBlock) k_core_rows(const int* __restrict__ ro
 // degrees are whole words and rows are padded: an entry costs about five instructions
 // instead of 14 with 16-bit degrees, bounds tests and an early exit each (which
 // took 5.7 ms on the 1M-vertex graph although they held half as many vertices again).
-__global__ void __launch_bounds__(kPeelBlock) k_core_peel(const int2* __restrict__ span,
+__global__ void __launch_bounds__(kPeelBlock) k_core_peel(const CoreSpan* __restrict__ span,
                                                          const unsigned short* __restrict__ rows,
                                                          const int* __restrict__ list, int* round_of, int* key,
                                                          int* ctl) {
@@ -613,7 +620,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_peel(const int2* __restrict
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     constexpr int NW = kPeelBlock / 64;
     const int L = ctl[CTL_CORE] < kCoreCap ? ctl[CTL_CORE] : kCoreCap;
-    for (int i = t; i < L; i += kPeelBlock) deg[i] = span[i].y;
+    for (int i = t; i < L; i += kPeelBlock) deg[i] = span[i].degree;
     int c = ctl[CTL_LEVEL], r = ctl[CTL_ROUNDS], degen = ctl[CTL_DEGEN];
     if (t == 0) {
         deg[kCoreCap] = INT_MAX;   // the padding: never falls to a level
@@ -639,14 +646,15 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_peel(const int2* __restrict
         return mn;
     };
     // four neighbours lose one degree each
-    auto update = [&](const ushort4& x) {
-        const int o0 = atomicSub(&deg[x.x], 1), o1 = atomicSub(&deg[x.y], 1);
-        const int o2 = atomicSub(&deg[x.z], 1), o3 = atomicSub(&deg[x.w], 1);
+    auto update = [&](const CoreIds& x) {
+        const int i0 = x.ab & 0xffffu, i1 = x.ab >> 16, i2 = x.cd & 0xffffu, i3 = x.cd >> 16;
+        const int o0 = atomicSub(&deg[i0], 1), o1 = atomicSub(&deg[i1], 1);
+        const int o2 = atomicSub(&deg[i2], 1), o3 = atomicSub(&deg[i3], 1);
         if (o0 == c + 1 || o1 == c + 1 || o2 == c + 1 || o3 == c + 1) {
-            if (o0 == c + 1) push(x.x);
-            if (o1 == c + 1) push(x.y);
-            if (o2 == c + 1) push(x.z);
-            if (o3 == c + 1) push(x.w);
+            if (o0 == c + 1) push(i0);
+            if (o1 == c + 1) push(i1);
+            if (o2 == c + 1) push(i2);
+            if (o3 == c + 1) push(i3);
         }
     };
     // the frontier that the whole-device rounds left behind (none at a level change)
@@ -676,15 +684,15 @@ __global__ void __launch_bounds__(kPeelBlock) k_core_peel(const int2* __restrict
         }
         for (int i = head + t; i < tail; i += kPeelBlock) round_of[i] = r;
         for (int i = head + wave; i < tail; i += NW) {
-            const int2 sp = span[queue[i]];
-            const int b = __builtin_amdgcn_readfirstlane(sp.x);
-            const int e = b + ((__builtin_amdgcn_readfirstlane(sp.y) + 3) & ~3);
+            const CoreSpan sp = span[queue[i]];
+            const int b = __builtin_amdgcn_readfirstlane(sp.at);
+            const int e = b + ((__builtin_amdgcn_readfirstlane(sp.degree) + 3) & ~3);
             for (int j0 = b; j0 < e; j0 += 512) {
                 const int j = j0 + 4 * lane;
                 const bool two = j0 + 256 < e;
-                ushort4 x0{}, x1{};
-                if (j < e) x0 = *reinterpret_cast<const ushort4*>(rows + j);
-                if (two && j + 256 < e) x1 = *reinterpret_cast<const ushort4*>(rows + j + 256);
+                CoreIds x0{}, x1{};
+                if (j < e) x0 = *reinterpret_cast<const CoreIds*>(rows + j);
+                if (two && j + 256 < e) x1 = *reinterpret_cast<const CoreIds*>(rows + j + 256);
                 if (j < e) update(x0);
                 if (two && j + 256 < e) update(x1);
             }
@@ -1562,11 +1570,7 @@ extern "C" KC_API size_t kc_orient_workspace(int32_t n, int32_t nnz, int32_t ord
 }
 
 namespace {
-bool invalid(const int* hctl) {
-    long long up = 0;
-    std::memcpy(&up, hctl + CTL_UP, sizeof(up));
-    return hctl[CTL_BAD] != 0 || up != 0;
-}
+bool invalid(const int* hctl) { return hctl[CTL_BAD] != 0 || hctl[CTL_UP] != 0; }
 }  // namespace
 
 extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out, void* ws,
@@ -1683,7 +1687,7 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
             k_peel_init<<<grid_for_threads(n), kBlock, 0, s>>>(n, g->row_ptr, deg, w.key_a, w.val_a, w.ctl);
         }
         unsigned short* rows = reinterpret_cast<unsigned short*>(w.outdeg);   // outdeg, rnd, tmp: nnz + 4 n entries
-        int2* span = reinterpret_cast<int2*>(w.hf0);   // hf0 and hf1 are adjacent: 2 n ints and more
+        CoreSpan* span = reinterpret_cast<CoreSpan*>(w.hf0);   // hf0 and hf1 are adjacent: 2 n ints and more
         k_core_list<<<div_up(n, kPeelBlock), kPeelBlock, 0, s>>>(n, w.key_a, deg, w.rank, w.fr0, span, w.ctl);
         k_core_rows<<<grid_for_waves(n < kCoreCap ? n : kCoreCap), kBlock, 0, s>>>(
             g->row_ptr, g->col, w.rank, w.fr0, span, rows, w.ctl);
