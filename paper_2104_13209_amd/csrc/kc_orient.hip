@@ -12,6 +12,7 @@
 //   compact   gather each kept row, sort it by new id, write col and the COO src
 #include <climits>
 
+#include "kc_barrier.h"
 #include "kc_internal.h"
 
 namespace kc {
@@ -289,15 +290,16 @@ __device__ __forceinline__ void st_agent(T* p, T v) {
 // (s_waitcnt) when the block arrives; no cache is written back or invalidated.
 // 1.3 us at 64 blocks (cooperative groups: 8.7).  False once a wait ran out, after
 // which every block leaves.
-__device__ __forceinline__ bool peel_barrier(int* bar, int& epoch, int* shared_ok) {
+__device__ __forceinline__ bool peel_barrier(int* bar, unsigned int& epoch, int* shared_ok) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     epoch++;
     if (threadIdx.x == 0) {
-        const int want = epoch * static_cast<int>(gridDim.x);
+        const unsigned int want = epoch * gridDim.x;
         __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int spins = 0;
-        while (ld_acquire(bar) < want && ++spins < kPeelSpins) __builtin_amdgcn_s_sleep(1);
+        while (arrivals_missing(static_cast<unsigned int>(ld_acquire(bar)), want) && ++spins < kPeelSpins)
+            __builtin_amdgcn_s_sleep(1);
         *shared_ok = spins < kPeelSpins;
     }
     __syncthreads();
@@ -377,7 +379,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
     const int wave = tid >> 6;
     const int nwaves = nth >> 6;
     int* bar = ctl + CTL_BAR;
-    int epoch = 0;
+    unsigned int epoch = 0;
     if (rejected(ctl)) return;
 
     for (int v = tid; v < n; v += nth) {
