@@ -196,7 +196,10 @@ KC_API size_t kc_orient_workspace(int32_t n, int32_t nnz, int32_t order);
  * synchronises `stream`.  validate != 0 first checks that g is a sorted simple
  * symmetric CSR and returns KC_EINVAL if not; with validate == 0 a malformed
  * graph gives an unspecified DAG.  Returns KC_ENOMEM if ws_bytes is below
- * kc_orient_workspace(). */
+ * kc_orient_workspace().  The degeneracy order of more than 4,000 vertices has one
+ * launch of up to 64 workgroups that all have to run at once: where other streams'
+ * work holds the compute units, the call waits until it has ended, however long.
+ * KC_EDEVICE is returned when such a launch stops making progress once it runs. */
 KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out, void* ws,
                          size_t ws_bytes, int32_t validate, void* stream);
 

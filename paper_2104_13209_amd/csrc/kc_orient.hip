@@ -36,7 +36,6 @@ enum Ctl {
     CTL_MIN = 11,      // peel level minimum
     CTL_LEVEL = 12,    // peel: current level
     CTL_CORE = 13,     // peel: vertices left for the one-workgroup rounds
-    CTL_DONE = 14,     // peel: the whole-device rounds ended regularly
     CTL_CORE_AT = 15,  // peel: entries of the compacted rows
     CTL_CL_SIZE0 = 8,  // colouring: light frontier sizes, ring of 3 (8, 9, 10; not used with the peel)
     CTL_CL_HSIZE0 = 12,// colouring: heavy frontier sizes, ring of 3 (12, 13, 14)
@@ -44,8 +43,13 @@ enum Ctl {
     CTL_AD_SUM = 18,   // approximate degeneracy: their degree sum (u64 over words 18, 19)
     CTL_BAR = 32,      // peel: barrier arrivals, on a cache line of their own
     CTL_UP = 34,       // validation: entries to longer rows less those to shorter ones (at most nnz < 2^31)
+    CTL_STALL = 36,    // peel: barrier waits that ran out (kStall* bits)
     CTL_WORDS = 64
 };
+
+// A launch's first barrier is passed when all its blocks run, for which they may have to wait
+// for other streams' work: the peel is launched again.  Later ones wait for nothing else.
+constexpr int kStallStart = 1, kStallLater = 2;
 
 // ------------------------------------------------------------ validation
 
@@ -201,9 +205,10 @@ __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per,
     }
 }
 
-// An invalid graph: nothing after the validation may follow its indices.
+// An invalid graph: nothing after the validation may follow its indices.  A peel that was
+// given up: nothing after it may follow keys and ids that were not written.
 __device__ __forceinline__ bool rejected(const int* ctl) {
-    return ctl[CTL_BAD] != 0 || ctl[CTL_UP] != 0;
+    return ctl[CTL_BAD] != 0 || ctl[CTL_UP] != 0 || ctl[CTL_STALL] != 0;
 }
 
 // --------------------------------------------------------------- keys
@@ -289,8 +294,9 @@ __device__ __forceinline__ void st_agent(T* p, T v) {
 // are served past the XCDs' L2s, so it is enough that they have been performed
 // (s_waitcnt) when the block arrives; no cache is written back or invalidated.
 // 1.3 us at 64 blocks (cooperative groups: 8.7).  False once a wait ran out, after
-// which every block leaves.
-__device__ __forceinline__ bool peel_barrier(int* bar, unsigned int& epoch, int* shared_ok) {
+// which every block leaves, and CTL_STALL says so.
+__device__ __forceinline__ bool peel_barrier(int* ctl, unsigned int& epoch, int* shared_ok) {
+    int* bar = ctl + CTL_BAR;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     epoch++;
@@ -301,6 +307,7 @@ __device__ __forceinline__ bool peel_barrier(int* bar, unsigned int& epoch, int*
         while (arrivals_missing(static_cast<unsigned int>(ld_acquire(bar)), want) && ++spins < kPeelSpins)
             __builtin_amdgcn_s_sleep(1);
         *shared_ok = spins < kPeelSpins;
+        if (spins >= kPeelSpins) atomicOr(&ctl[CTL_STALL], epoch == 1 ? kStallStart : kStallLater);
     }
     __syncthreads();
     return *shared_ok != 0;
@@ -378,7 +385,6 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
     const int lane = threadIdx.x & 63;
     const int wave = tid >> 6;
     const int nwaves = nth >> 6;
-    int* bar = ctl + CTL_BAR;
     unsigned int epoch = 0;
     if (rejected(ctl)) return;
 
@@ -392,7 +398,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
         count = 0;
         least = INT_MAX;
     }
-    if (!peel_barrier(bar, epoch, &ok)) return;
+    if (!peel_barrier(ctl, epoch, &ok)) return;
 
     int removed = 0, r = 0, c = -1, degen = 0;
     int recent = n;                                  // goes to 32 times the frontier size of late
@@ -423,7 +429,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
                 if (least != INT_MAX) atomicMin(&ctl[CTL_MIN], least);
                 least = INT_MAX;
             }
-            if (!peel_barrier(bar, epoch, &ok)) return;
+            if (!peel_barrier(ctl, epoch, &ok)) return;
             const int old = c;
             c = ld_acquire(&ctl[CTL_MIN]);
             if (c != old + 1) {
@@ -433,7 +439,7 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
                 }
             }
             if (c != old + 1) peel_flush(nx, &base);
-            if (!peel_barrier(bar, epoch, &ok)) return;
+            if (!peel_barrier(ctl, epoch, &ok)) return;
             if (tid == 0) st_agent(&ctl[CTL_MIN], INT_MAX);   // every read of it is behind the last barrier
             degen = c > degen ? c : degen;
             r++;
@@ -483,14 +489,13 @@ __global__ void __launch_bounds__(kPeelBlock) k_peel(int n, int keep, const int*
         removed += fsize;
         recent += fsize - recent / 32;
         r++;
-        if (!peel_barrier(bar, epoch, &ok)) return;
+        if (!peel_barrier(ctl, epoch, &ok)) return;
     }
     if (tid == 0) {
         ctl[CTL_DEGEN] = degen;
         ctl[CTL_LEVEL] = c;
         ctl[CTL_ROUNDS] = r;
         ctl[CTL_MAXKEY] = r > 0 ? r - 1 : 0;
-        ctl[CTL_DONE] = 1;
     }
 }
 
@@ -503,10 +508,7 @@ __global__ void __launch_bounds__(kBlock) k_peel_init(int n, const int* __restri
         key[v] = -1;
         val[v] = v;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl[CTL_LEVEL] = -1;
-        ctl[CTL_DONE] = 1;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl[CTL_LEVEL] = -1;
 }
 
 // Local ids of the vertices left (cid[v], -1 for the others; list[id] = v) and
@@ -1519,6 +1521,42 @@ int build_dag(const OrientWs& w, int n, int nnz, const int* row_ptr, const int* 
     return KC_OK;
 }
 
+// Degeneracy order: the peel's keys (rounds) and ids, and its control words.
+int launch_peel(const OrientWs& w, int n, const int* row_ptr, const int* col, hipStream_t s) {
+    int* deg = w.key_b;   // scratch until the sort
+    if (n > kCoreSmall) {
+        // one block per 16k vertices, between 16 and 64 (a barrier costs 0.8 us at
+        // 16 blocks, 1.3 at 64, 3.7 at 256, whatever the block size)
+        int occ = 0;
+        KC_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_peel, kPeelBlock, 0));
+        if (occ < 1) return KC_EDEVICE;
+        int blocks = n / 16384;
+        if (blocks > 64) blocks = 64;
+        if (blocks < 16) blocks = 16;
+        if (blocks > occ * device_cus()) blocks = occ * device_cus();   // all blocks co-resident
+        int n_ = n, keep = kCoreCap;
+        const int* rp = row_ptr;
+        const int* cl = col;
+        OrientWs ws = w;
+        void* args[] = {&n_, &keep, &rp, &cl, &deg, &ws.key_a, &ws.fr0, &ws.fr1, &ws.val_a, &ws.ctl};
+        KC_CHECK(hipLaunchCooperativeKernel(reinterpret_cast<void*>(k_peel), dim3(blocks), dim3(kPeelBlock),
+                                            args, 0, s));
+    } else {
+        k_peel_init<<<grid_for_threads(n), kBlock, 0, s>>>(n, row_ptr, deg, w.key_a, w.val_a, w.ctl);
+    }
+    unsigned short* rows = reinterpret_cast<unsigned short*>(w.outdeg);   // outdeg, rnd, tmp: nnz + 4 n entries
+    CoreSpan* span = reinterpret_cast<CoreSpan*>(w.hf0);   // hf0 and hf1 are adjacent: 2 n ints and more
+    k_core_list<<<div_up(n, kPeelBlock), kPeelBlock, 0, s>>>(n, w.key_a, deg, w.rank, w.fr0, span, w.ctl);
+    k_core_rows<<<grid_for_waves(n < kCoreCap ? n : kCoreCap), kBlock, 0, s>>>(
+        row_ptr, col, w.rank, w.fr0, span, rows, w.ctl);
+    const int lds = kCoreLds;
+    KC_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_core_peel),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    k_core_peel<<<1, kPeelBlock, lds, s>>>(span, rows, w.fr0, w.fr1, w.key_a, w.ctl);
+    KC_CHECK(hipGetLastError());
+    return KC_OK;
+}
+
 __global__ void __launch_bounds__(kBlock) k_zero(int* p, int count) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) p[i] = 0;
 }
@@ -1667,48 +1705,27 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
         KC_CHECK(hipMemcpyAsync(w.ctl + CTL_MAXKEY, &maxkey, sizeof(int), hipMemcpyHostToDevice, s));
         KC_CHECK(hipMemcpyAsync(w.ctl + CTL_ROUNDS, &r, sizeof(int), hipMemcpyHostToDevice, s));
         KC_CHECK(hipMemcpyAsync(w.key_a, w.rnd, sizeof(int) * n, hipMemcpyDeviceToDevice, s));
-    } else {
-        int* deg = w.key_b;   // scratch until the sort
-        if (n > kCoreSmall) {
-            // one block per 16k vertices, between 16 and 64 (a barrier costs 0.8 us at
-            // 16 blocks, 1.3 at 64, 3.7 at 256, whatever the block size)
-            int occ = 0;
-            KC_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_peel, kPeelBlock, 0));
-            if (occ < 1) return KC_EDEVICE;
-            int blocks = n / 16384;
-            if (blocks > 64) blocks = 64;
-            if (blocks < 16) blocks = 16;
-            if (blocks > occ * device_cus()) blocks = occ * device_cus();   // all blocks co-resident
-            int n_ = n, keep = kCoreCap;
-            const int* rp = g->row_ptr;
-            const int* cl = g->col;
-            void* args[] = {&n_, &keep, &rp, &cl, &deg, &w.key_a, &w.fr0, &w.fr1, &w.val_a, &w.ctl};
-            KC_CHECK(hipLaunchCooperativeKernel(reinterpret_cast<void*>(k_peel), dim3(blocks), dim3(kPeelBlock),
-                                                args, 0, s));
-        } else {
-            k_peel_init<<<grid_for_threads(n), kBlock, 0, s>>>(n, g->row_ptr, deg, w.key_a, w.val_a, w.ctl);
-        }
-        unsigned short* rows = reinterpret_cast<unsigned short*>(w.outdeg);   // outdeg, rnd, tmp: nnz + 4 n entries
-        CoreSpan* span = reinterpret_cast<CoreSpan*>(w.hf0);   // hf0 and hf1 are adjacent: 2 n ints and more
-        k_core_list<<<div_up(n, kPeelBlock), kPeelBlock, 0, s>>>(n, w.key_a, deg, w.rank, w.fr0, span, w.ctl);
-        k_core_rows<<<grid_for_waves(n < kCoreCap ? n : kCoreCap), kBlock, 0, s>>>(
-            g->row_ptr, g->col, w.rank, w.fr0, span, rows, w.ctl);
-        const int lds = kCoreLds;
-        KC_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k_core_peel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        k_core_peel<<<1, kPeelBlock, lds, s>>>(span, rows, w.fr0, w.fr1, w.key_a, w.ctl);
-        KC_CHECK(hipGetLastError());
     }
     // 2. stable radix sort (key, id) -> position = new id; 3. filter: out-degrees and
     // their scan -> row_ptr; 4. compact + per-row sort.  Degrees and colours are below
     // n; the peel's rounds below 2 n, as a level change counts as one.
-    int st = build_dag(w, n, nnz, g->row_ptr, g->col, order == KC_ORDER_DEGENERACY ? 2LL * n : n, false, m,
-                       out->row_ptr, out->col, out->src, out->perm, s);
-    if (st != KC_OK) return st;
-    KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
-    KC_CHECK(hipStreamSynchronize(s));
-    if (invalid(hctl)) return KC_EINVAL;
-    if (order == KC_ORDER_DEGENERACY && !hctl[CTL_DONE]) return KC_EDEVICE;   // a barrier wait ran out
+    for (;;) {
+        if (order == KC_ORDER_DEGENERACY) {
+            const int st = launch_peel(w, n, g->row_ptr, g->col, s);
+            if (st != KC_OK) return st;
+        }
+        const int st = build_dag(w, n, nnz, g->row_ptr, g->col, order == KC_ORDER_DEGENERACY ? 2LL * n : n, false, m,
+                                 out->row_ptr, out->col, out->src, out->perm, s);
+        if (st != KC_OK) return st;
+        KC_CHECK(hipMemcpyAsync(hctl, w.ctl, sizeof(hctl), hipMemcpyDeviceToHost, s));
+        KC_CHECK(hipStreamSynchronize(s));
+        if (invalid(hctl)) return KC_EINVAL;
+        if (!(hctl[CTL_STALL] & kStallStart)) break;
+        // other streams' work held the compute units for all of the first barrier's wait
+        // (seconds): wait on
+        KC_CHECK(hipMemsetAsync(w.ctl, 0, CTL_WORDS * sizeof(int), s));
+    }
+    if (hctl[CTL_STALL]) return KC_EDEVICE;   // a later barrier's wait ran out
     if (hctl[CTL_LONG]) {
         k_sort_long_rows<<<grid_for_threads(n), kBlock, 0, s>>>(n, out->row_ptr, w.tmp, out->col, out->src, w.ctl);
         KC_CHECK(hipGetLastError());
