@@ -26,7 +26,7 @@ int lane_launch(const LaneLaunch& L, hipStream_t s) {
     P.gacc = L.gacc;
     P.gid = L.gid;
     P.steal = L.pair && L.steal;
-    P.helper = L.helper && P.steal;
+    P.helper = L.helper && L.pair;
     P.qctl = L.qctl;
     P.qready = L.qready;
     P.qitems = L.qitems;

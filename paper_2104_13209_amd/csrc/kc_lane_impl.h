@@ -62,7 +62,8 @@ struct LaneParams {
     unsigned long long* gacc;       // batched: per-graph {lo, hi}; null otherwise
     const int* __restrict__ gid;    // batched: graph of each DAG vertex
     bool steal;                     // pair mode: subtree queue between wavefronts
-    bool helper;                    // joins a running launch: no roots of its own, no waiter cap
+    bool helper;                    // joins a running launch: roots only from the queue (with handoff none), no
+                                    // registry entries, no waiter cap
     int* qctl;                      // queue control words (zero at launch)
     int* qready;                    // per ring slot (zero at launch): g*cap free for the producer of
                                     // generation g, g*cap + 1 written, (g+1)*cap read
@@ -236,7 +237,7 @@ __device__ __forceinline__ void walk_root(const LaneParams& P, int k, int p0, in
         if (lane == 0) pre[s] = run;
         wave_sync_lds();
         total = run;
-        if (!helping && lane == 0) {
+        if (!helping && !P.helper && lane == 0) {   // the registry's entries are the main launch's
             __hip_atomic_store(&ttot[slot], run + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&P.active[blockIdx.x], slot, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -632,8 +633,9 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
     unsigned long long acc = 0, nodes = 0, wsum = 0, iters = 0, exps = 0, idle = 0, cw = 0;
     const unsigned long long t_begin = STATS ? __builtin_amdgcn_s_memrealtime() : 0ull;
     if (steal && lane == 0) atomicAdd(&q[Q_ROOTING], 1);    // in the root phase
-    bool helping = steal && P.helper;               // helpers own no roots (and no registry entry)
+    bool helping = steal && P.helper;
     RootClaims rc;
+    rc.started = P.helper;                          // the first roots, by wavefront index, are the main launch's
     int claims = 0;                                 // roots walked since the last cancel poll
 
     // ---------------------------------------------- root phase
@@ -672,7 +674,7 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
         run_root<MAXW, EC, PAIR, STATS>(P, roots, k, p0, slot, helping, nullptr, 0, false, ctl, S, B, pre, mbox, stk,
                                         tctr, ttot, lt, acc, nodes, wsum, iters, exps, cw);
         cur = slot;
-        if (PAIR && !helping && lane == 0)
+        if (PAIR && !helping && !P.helper && lane == 0)
             __hip_atomic_store(&P.active[blockIdx.x], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (P.gacc) flush_root(P, graph, acc);
         wave_sync_lds();
