@@ -63,7 +63,7 @@ struct LaneParams {
     const int* __restrict__ gid;    // batched: graph of each DAG vertex
     bool steal;                     // pair mode: subtree queue between wavefronts
     bool helper;                    // joins a running launch: roots only from the queue (with handoff none), no
-                                    // registry entries, no waiter cap
+                                    // registry entries
     int* qctl;                      // queue control words (zero at launch)
     int* qready;                    // per ring slot (zero at launch): g*cap free for the producer of
                                     // generation g, g*cap + 1 written, (g+1)*cap read
@@ -700,11 +700,16 @@ __global__ void __launch_bounds__(64) k_lane(LaneParams P) {
     // both reading zero (rooting first) means no work can appear any more.
     if (steal) {
         if (lane == 0) __hip_atomic_fetch_add(&q[Q_ROOTING], -1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        // at most kMaxWaiters wavefronts wait; the others end here and free their
-        // compute unit slots for launches that run beside this one.  A waiter
-        // leaves only at the end, so handed-over subtrees always find one.
+        // at most kMaxWaiters wavefronts wait, the helper's among them; the others end here
+        // and free their compute unit slots for launches that run beside this one.  A waiter
+        // leaves only at the end, so handed-over subtrees always find one.  Each of
+        // them loads four words of the queue's line every 100 us or so, 11.6 ns each: 2,300
+        // fill it, and the wavefronts that work wait for it too.  A helper of 6,000 waiters
+        // that came before the main launch's end: k = 9, vertex roots, of a 200k-vertex
+        // power-law graph 155 ms with 256 waiters in all, 163 with 512, 226 with 2,048, 440 with
+        // all; k = 10 of the 1M-vertex one 262, 262, 263 and 261.
         int stay = 1;
-        if (lane == 0 && atomicAdd(&q[Q_HUNGRY], 1) >= kMaxWaiters && !P.helper) {
+        if (lane == 0 && atomicAdd(&q[Q_HUNGRY], 1) >= kMaxWaiters) {
             atomicAdd(&q[Q_HUNGRY], -1);
             stay = 0;
         }
