@@ -132,7 +132,8 @@ typedef struct kc_profile {
 /* Flags of kc_opts:
  * KC_OPT_NO_HANDOFF      wavefronts never hand subtrees to idle wavefronts;
  * KC_OPT_SINGLE_STREAM   every launch stays on the caller's stream (no side
- *                        stream for the widest root list, no helper launch):
+ *                        stream for the widest root list or the pivot's middle
+ *                        one, no helper launch):
  *                        for callers that already run many counts at once;
  * KC_OPT_NO_BITSETS      non-pivot counts without binary encoding (the
  *                        ablation of Sec. 4.3): candidate sets are sorted vertex
@@ -214,7 +215,8 @@ KC_API size_t kc_count_workspace(const kc_dag* d, int32_t k, int32_t pivot, cons
  *               KC_EOVERFLOW at 2^128 or more.
  * k < 1 is KC_EINVAL; k = 1 gives n and k = 2 gives m.  Synchronises `stream`.
  * Deep non-pivot counts run the widest root list on an auxiliary stream of the
- * library's own (fork and join by events on `stream`) unless KC_OPT_SINGLE_STREAM
+ * library's own (fork and join by events on `stream`), and pivot counts with
+ * d_max > 128 that of the candidate sets of 65 to 128, unless KC_OPT_SINGLE_STREAM
  * is set; wavefronts hand work to idle ones through the workspace's queues unless
  * KC_OPT_NO_HANDOFF is set.  KC_EDEVICE is returned when such a queue stops making
  * progress for 20 s (no count is valid then).  One workspace serves one call at a

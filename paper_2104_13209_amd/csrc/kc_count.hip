@@ -832,18 +832,33 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         L.src = d->src;
         L.w = w;
         if (mid_cap > 0) {
-            // totals: search state in registers for up to kMidCap candidates; queue
-            // items of the middle and the heavy launch share a region in turn
+            // Totals: search state in registers for up to kMidCap candidates.  The middle list
+            // beside the heavy one: each ends with its longest tree (600 vertices at density 0.3,
+            // every size: 26 ms when one launch had both, 36 in turn, 25 so).
             st = pivot_reg_launch(L, false, s);
             if (st != KC_OK) return st;
             if (prof) KC_CHECK(hipEventRecord(pe->ev[2], s));
+            SideGuard side;
+            hipStream_t ms = s;
+            if (dm > mid_cap && !(o && (o->flags & KC_OPT_SINGLE_STREAM))) {
+                st = side_acquire(&side.s);
+                if (st != KC_OK) return st;
+                side.held = true;
+                ms = side.s.stream;
+                KC_CHECK(hipEventRecord(side.s.fork, s));
+                KC_CHECK(hipStreamWaitEvent(ms, side.s.fork, 0));
+            }
             if (dm > kLightCap) {
-                st = pivot_reg_launch(L, true, s);
+                st = pivot_reg_launch(L, true, ms);
                 if (st != KC_OK) return st;
             }
             if (dm > mid_cap) {
                 st = pivot_launch(L, true, s);
                 if (st != KC_OK) return st;
+            }
+            if (side.held) {
+                KC_CHECK(hipEventRecord(side.s.join, ms));
+                KC_CHECK(hipStreamWaitEvent(s, side.s.join, 0));
             }
             st = pivot_leaves_launch(L, s);
             if (st != KC_OK) return st;

@@ -625,7 +625,7 @@ int pivot_reg_launch(const PivLaunch& L, bool mid, hipStream_t s) {
     P.stats = w.acc + (mid ? 4 : 2);
     P.qctl = w.qctl + kShardLine * kRegShards * queue;
     P.qready = w.qready + static_cast<size_t>(kQueueCap) * queue;
-    P.qitems = w.qitems + (mid ? static_cast<size_t>(kQueueCap) * kItemWords : 0);
+    P.qitems = w.qitems;   // the light launch has ended when the middle one begins; the heavy one has the other region
     P.cancel = L.cancel;
     if (mid) {
         if (L.ec) return L.all ? launch_reg<2, true, true, 16>(P, L.stats, s) : launch_reg<2, true, false, 16>(P, L.stats, s);
