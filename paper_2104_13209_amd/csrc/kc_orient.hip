@@ -60,11 +60,15 @@ constexpr int kStallStart = 1, kStallLater = 2;
 // share cache lines, k_fill 4.6 -> 3.3 ms on the batch of 10,000).  Each wavefront loads the bounds of its `per` rows a lane each
 // and walks rows of up to kLongRow entries four at a time, 16 lanes each: an average
 // row has some 32 entries, and a wavefront per row waits on one chain of loads for
-// each.  Longer rows go to a list in LDS that the whole block then shares.
+// each.  Longer rows go to a list in LDS: those of up to kBlockRow entries are taken by a
+// wavefront each, the others by the whole block (all of them by the block: graphs of
+// 100,000 vertices and mean degree 300 took 1,340 us from sort to rows, with a wavefront
+// per row before 911).
 constexpr int kRowBlock = 1024;
 constexpr int kLongRow = 256;
+constexpr int kBlockRow = 2048;
 constexpr int kMaxPer = 64;
-constexpr int kRowRun = 16;
+constexpr int kRowRun = 4;
 
 struct LongRows {
     int n;
@@ -189,8 +193,9 @@ __global__ void __launch_bounds__(kRowBlock) k_validate(int n, int nnz, int per,
     });
     __syncthreads();
     for (int l = 0; l < longs.n; l++) {
+        // 64 entries a wavefront; the next row starts eleven wavefronts on, as rows of this list may be short of 16 slices
         const int v = longs.row[l], first = row_ptr[v], last = row_ptr[v + 1];
-        for (int j = first + (threadIdx.x & ~63); j < last; j += kRowBlock)
+        for (int j = first + 64 * (((threadIdx.x >> 6) + 11 * l) & 15); j < last; j += kRowBlock)
             check(v, last - first, first, j + lane, j + lane < last);
     }
     wave_sync_lds();
@@ -1229,9 +1234,27 @@ __global__ void __launch_bounds__(kRowBlock) k_outdeg(int n, int per, int run, c
     wave_sync_lds();
     if (i >= 0 && e - b <= kLongRow) outdeg[i] = cnt[lane];
     __syncthreads();
+    for (int l = threadIdx.x >> 6; l < longs.n; l += kRowBlock / 64) {
+        const int row = longs.row[l], v = perm[row];
+        const int first = row_ptr[v], last = row_ptr[v + 1];
+        if (last - first > kBlockRow) continue;
+        int c = 0;
+        for (int j0 = first; j0 < last; j0 += 256) {
+            int r[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = j0 + 64 * u + lane < last ? col[j0 + 64 * u + lane] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = r[u] >= 0 ? rank[r[u]] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) c += r[u] > row;
+        }
+        c = wave_sum(c);
+        if (lane == 0) outdeg[row] = c;
+    }
     for (int l = 0; l < longs.n; l++) {
         const int row = longs.row[l], v = perm[row];
         const int last = row_ptr[v + 1];
+        if (last - row_ptr[v] <= kBlockRow) continue;
         if (threadIdx.x == 0) cnt_all[0][0] = 0;
         __syncthreads();
         int c = 0;
@@ -1247,11 +1270,13 @@ __global__ void __launch_bounds__(kRowBlock) k_outdeg(int n, int per, int run, c
 // Gathers row i's kept neighbours (as new ids) into LDS, then places each at its
 // rank within the row (count of smaller entries): col[] rows come out sorted.  Rows
 // of up to kLongRow neighbours of which at most kGroupRow are kept are handled by 16
-// lanes, the others by the whole block.  Rows of more than kRowCap kept neighbours
+// lanes, those of up to kBlockRow of which at most kWaveRow are kept by a wavefront, the
+// others by the whole block.  Rows of more than kRowCap kept neighbours
 // go to tmp[] unsorted and are finished by k_sort_long_rows.  Bound by the gathers of ranks.
 // Nothing is written when the rows hold more than `room` entries, which happens only on a
 // graph that lacks reverse entries (and was not validated).
 constexpr int kGroupRow = 64;
+constexpr int kWaveRow = 4 * (kGroupRow + 16) - 4;   // the buffers of a wavefront's four groups, less the filling
 
 __global__ void __launch_bounds__(kRowBlock) k_fill(int n, int per, int run, const int* __restrict__ row_ptr,
                                                    const int* __restrict__ col, const int* __restrict__ perm,
@@ -1325,10 +1350,46 @@ __global__ void __launch_bounds__(kRowBlock) k_fill(int n, int per, int run, con
         wave_sync_lds();
     }
     __syncthreads();
+    int* wrow = groups[(threadIdx.x >> 6) * 4];
+    for (int l = threadIdx.x >> 6; l < longs.n; l += kRowBlock / 64) {
+        const int i = longs.row[l], v = perm[i];
+        const int base = dag_ptr[i], rlen = dag_ptr[i + 1] - base;
+        const int first = row_ptr[v], last = row_ptr[v + 1];
+        if (rlen > kWaveRow || last - first > kBlockRow) continue;
+        int pos = 0;
+        for (int j0 = first; j0 < last; j0 += 256) {
+            int r[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = j0 + 64 * u + lane < last ? col[j0 + 64 * u + lane] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) r[u] = r[u] >= 0 ? rank[r[u]] : -1;
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const unsigned long long m = __ballot(r[u] > i);
+                const int p = pos + __popcll(m & lanemask_lt());
+                if (r[u] > i && p < rlen) wrow[p] = r[u];
+                pos += __popcll(m);
+            }
+        }
+        if (lane < 4) wrow[rlen + lane] = INT_MAX;
+        wave_sync_lds();
+        for (int t = lane; t < rlen; t += 64) {
+            const int x = wrow[t];
+            int below = 0;
+            for (int u = 0; u < rlen; u += 4) {
+                const int4 y = *reinterpret_cast<const int4*>(wrow + u);
+                below += (y.x < x) + (y.y < x) + (y.z < x) + (y.w < x);
+            }
+            dag_col[base + below] = x;
+            dag_src[base + t] = i;
+        }
+        wave_sync_lds();
+    }
     for (int l = 0; l < longs.n; l++) {
         const int i = longs.row[l], v = perm[i];
         const int base = dag_ptr[i], rlen = dag_ptr[i + 1] - base;
         const int last = row_ptr[v + 1];
+        if (rlen <= kWaveRow && last - row_ptr[v] <= kBlockRow) continue;
         const bool in_lds = rlen <= kRowCap;
         int* dst = in_lds ? big_row : tmp + base;
         if (threadIdx.x == 0) {
@@ -1456,8 +1517,11 @@ int grid_for_waves(long long items_per_wave_units) {
 }
 
 // Rows per wavefront of the row kernels: about four blocks per CU, 4 (one per group
-// of 16 lanes) to 64 rows, a power of two.
-int rows_per_wave(int n) {
+// of 16 lanes) to 64 rows, a power of two.  One where most rows are long: the groups have
+// little to do then, and few blocks would share the rows (every vertex of 4,000 joined to
+// half of the others: 63 blocks, k_validate 1,070 us; 250, 290; 339 with a wavefront per row).
+int rows_per_wave(int n, int nnz) {
+    if (nnz / n > kLongRow) return 1;
     const int per = n / (16 * 4 * device_cus());
     int p = 4;
     while (p < kMaxPer && 2 * p <= per) p *= 2;
@@ -1499,7 +1563,7 @@ int build_dag(const OrientWs& w, int n, int nnz, const int* row_ptr, const int* 
               int room, int* out_row_ptr, int* out_col, int* out_src, int* out_perm, hipStream_t s) {
     const int ntiles = div_up(n, kTile);
     const RadixBuf rb{w.key_a, w.val_a, w.key_b, w.val_b};
-    const int per = rows_per_wave(n), rows_grid = div_up(n, 16 * per);
+    const int per = rows_per_wave(n, nnz), rows_grid = div_up(n, 16 * per);
     const int run = grouped ? 16 * per : kRowRun;
     int *dtot = w.tiles, *hist = w.tiles + 256;
     int pass = 0;
@@ -1645,8 +1709,8 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
     // Rejected graphs stop every later kernel on the device; the orders that read back
     // on the way look at the verdict first.
     if (validate) {
-        const int per = rows_per_wave(n);
-        k_validate<<<div_up(n, 16 * per), kRowBlock, 0, s>>>(n, nnz, per, kRowRun, g->row_ptr, g->col, w.ctl);
+        const int per = rows_per_wave(n, nnz);
+        k_validate<<<div_up(n, 16 * per), kRowBlock, 0, s>>>(n, nnz, per, 1, g->row_ptr, g->col, w.ctl);
         KC_CHECK(hipGetLastError());
     }
     int hctl[CTL_WORDS];
