@@ -353,9 +353,12 @@ KC_API int32_t kc_batch_count(const kc_batch* b, int32_t k, uint64_t* counts, vo
  * (kc_count_workspace) fits in the server's device arena of `mem_budget` bytes,
  * and (unless no other query runs) the estimated LDS of the admitted queries
  * stays within the device's LDS (per query: one wavefront's LDS for its widest
- * root list or pivot kernel times the wavefronts it launches, at most one per
- * root); admitted queries run concurrently, one HIP stream per worker, so work of
- * queries that arrive while others run overlaps on the device.  A query that
+ * root list, or for the largest of its pivot launches with the wavefront's share of
+ * the block's, times the wavefronts it launches, at most one per root; pivot queries
+ * launch at most half the wavefronts that fit the device, a quarter of those for sets
+ * of at most 64 candidates while others run or wait); admitted queries run
+ * concurrently, one HIP stream per worker, so work of queries that arrive while
+ * others run overlaps on the device.  A query that
  * could never fit the arena completes at once with status KC_ENOMEM.
  * Ownership: the server allocates its arena and streams in kc_server_create and
  * frees them in kc_server_destroy (the only entry points that allocate device

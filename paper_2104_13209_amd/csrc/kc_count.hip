@@ -821,6 +821,8 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
         L.ec = ec;
         L.stats = stats;
         L.steal = !(o && (o->flags & KC_OPT_NO_HANDOFF));
+        L.share = o ? (o->flags >> kOptShareShift) & 3 : 0;
+        if (L.share > 2) L.share = 2;
         if (o) {
             L.steal_every = o->handoff_every > 0 ? o->handoff_every : 0;
             L.steal_after = o->handoff_after > 0 ? o->handoff_after : 0;
@@ -969,27 +971,38 @@ size_t device_lds_bytes() {
     return static_cast<size_t>(device_cus()) * static_cast<size_t>(per_cu);
 }
 
-size_t count_lds_demand(const kc_dag* d, int k, int pivot) {
+size_t count_lds_demand(const kc_dag* d, int k, int pivot, int share) {
     if (!d || k < 3 || d->m <= 0 || k > d->d_max + 1) return 0;
     const int dm = bit_dmax(d->d_max);
     const bool ec = pick_scheme(nullptr, k) == KC_SCHEME_EC;
     const long long roots = ec ? d->m : d->n;
-    size_t per_wave = 0;
-    long long waves = 0;
+    const size_t cap = device_lds_bytes();
+    auto launch = [&](size_t per_wave, long long waves) {
+        return per_wave * static_cast<size_t>(roots < waves ? roots : waves);
+    };
+    size_t most = 0;
     if (!pivot) {
         int top = 0;
         while (top < kWidthLists - 1 && (32 << top) < dm) top++;
-        per_wave = lane_lds_bytes(1 << top, k, ec, pair_list(k, ec, top));
-        waves = static_cast<long long>(device_cus()) * kLaneWavesPerCU;
+        most = launch(lane_lds_bytes(1 << top, k, ec, pair_list(k, ec, top)),
+                      static_cast<long long>(device_cus()) * kLaneWavesPerCU);
     } else {
-        const int s_cap = s_cap_for(dm), maxw = maxw_for(dm);
-        per_wave = static_cast<size_t>(8 + s_cap + s_cap * b_stride_of(maxw)) * 4;
-        waves = static_cast<long long>(device_cus()) * kPivBlocksPerCU;
+        const int cu_lds = static_cast<int>(cap / static_cast<size_t>(device_cus()));
+        int waves = 0;
+        size_t per_wave = pivot_reg_lds(false, share, cu_lds, &waves);
+        most = launch(per_wave, waves);
+        if (dm > kLightCap) {
+            per_wave = pivot_reg_lds(true, share, cu_lds, &waves);
+            size_t larger = launch(per_wave, waves);
+            if (dm > kMidCap) {
+                const int s_cap = s_cap_for(dm), maxw = maxw_for(dm);
+                larger += launch(static_cast<size_t>(8 + s_cap + s_cap * b_stride_of(maxw)) * 4,
+                                 static_cast<long long>(device_cus()) * kPivBlocksPerCU);
+            }
+            most = larger > most ? larger : most;
+        }
     }
-    if (roots < waves) waves = roots;
-    const size_t total = per_wave * static_cast<size_t>(waves);
-    const size_t cap = device_lds_bytes();
-    return total < cap ? total : cap;
+    return most < cap ? most : cap;
 }
 
 }  // namespace kc

@@ -87,6 +87,8 @@ enum CountCtl {
     CC_WORDS = 32
 };
 
+constexpr int kOptShareShift = 16;   // kc_opts.flags, set by the server: PivLaunch::share in two bits
+
 constexpr size_t kAccAfterCtl = 256;   // bytes from the control words to the accumulators
 
 // Saved levels a depth-first walk starting at path length `first` may need:
@@ -278,6 +280,7 @@ struct PivLaunch {
     bool ec;              // edge roots
     bool stats;
     bool steal;           // hand saved frames to idle wavefronts (queue regions 0 and 1)
+    int share = 0;        // 0: the whole device; a server's query, 1: alone, 2: beside others
     int steal_every = 0;                   // 0: the default (kPivStealEvery)
     int steal_after = 0;                   // 0: the default of the root list and scheme
     const int* cancel = nullptr;   // caller's cancel flag (null: none)
@@ -298,6 +301,9 @@ int pivot_launch(const PivLaunch& L, bool heavy, hipStream_t s);
 // turns into counts.
 int pivot_reg_launch(const PivLaunch& L, bool mid, hipStream_t s);
 int pivot_leaves_launch(const PivLaunch& L, hipStream_t s);
+// LDS bytes per wavefront of such a launch (its share of the block's leaf counters among
+// them), and the wavefronts that fit the device's compute units by LDS.
+size_t pivot_reg_lds(bool mid, int share, int cu_lds, int* waves);
 
 // Launch description for the lane-walk graph-orientation kernel (kc_lane.hip).
 struct LaneLaunch {
@@ -339,10 +345,10 @@ int lane_launch(const LaneLaunch& L, hipStream_t s);
 
 // On-chip memory a kc_count call keeps resident while it runs (an estimate for
 // admission): the LDS bytes of one wavefront of its dominant traversal kernel
-// (the widest width list's lane walk, or the heavy pivot kernel) times the
-// wavefronts that kernel launches (at most one per root), capped at the device's
-// LDS (kc_count.hip).
-size_t count_lds_demand(const kc_dag* d, int k, int pivot);
+// (the widest width list's lane walk, or the largest of the pivot launches, the middle
+// and the heavy one together) times the wavefronts that kernel launches (at most one per
+// root), capped at the device's LDS (kc_count.hip).  share: see PivLaunch.
+size_t count_lds_demand(const kc_dag* d, int k, int pivot, int share);
 size_t device_lds_bytes();
 
 // Sub-wavefront group walk (k_go, Sec. 3.5) over one width list of a batched

@@ -586,10 +586,27 @@ __global__ void __launch_bounds__(256) k_piv_leaves(int first, int most, int bin
     if (ovf) atomicOr(flags, kFlagBigBinom);
 }
 
+// LDS bytes of a block: leaf counters, then the wavefronts' regions.
+template <int H, int WPB>
+constexpr size_t reg_block_lds() {
+    return (2 * static_cast<size_t>(leaf_index(64 * H + 2, 0) + 64 * H + 3) + static_cast<size_t>(WPB) * reg_wave_words<H>()) * 4;
+}
+
+// Wavefronts per block of the light and of the middle launch.
+constexpr int kRegLightWaves = 4, kRegMidWaves = 16;
+
+// One block in this many of those that fit the device is launched, by PivLaunch::share: a
+// block keeps its LDS until its longest root is done, and the server admits queries by LDS.  48
+// mixed queries over 8 graphs of 30,000 vertices: 25.7 ms with all blocks (one pivot query
+// at a time), 20.9 with a half of either launch, 18.9 with a quarter of the light one's
+// (19.9 with a quarter of both); 67, 38, 26 and 26 ms where all are pivot queries.  A query
+// that is alone loses little by the half (k = 3 on 1M vertices 3.7 -> 4.2 ms, most
+// nothing), and others can join it.
+constexpr int kRegLightShare[3] = {1, 2, 4}, kRegMidShare[3] = {1, 2, 2};
+
 template <int H, bool EC, bool ALL, int WPB>
-int launch_reg(const PivRegParams& P, bool stats, hipStream_t s) {
-    constexpr int LEAVES = leaf_index(64 * H + 2, 0) + 64 * H + 3;
-    const size_t lds = (2 * static_cast<size_t>(LEAVES) + static_cast<size_t>(WPB) * reg_wave_words<H>()) * 4;
+int launch_reg(const PivRegParams& P, bool stats, int share, hipStream_t s) {
+    constexpr size_t lds = reg_block_lds<H, WPB>();
     auto kern = stats ? k_piv_reg<H, EC, ALL, WPB, true> : k_piv_reg<H, EC, ALL, WPB, false>;
     if (lds > 64 * 1024)
         KC_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -597,7 +614,7 @@ int launch_reg(const PivRegParams& P, bool stats, hipStream_t s) {
     int occ = 0;
     KC_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * WPB, lds));
     if (occ < 1) return KC_EUNSUPPORTED;
-    kern<<<device_cus() * occ, 64 * WPB, lds, s>>>(P);
+    kern<<<div_up(device_cus() * occ, share), 64 * WPB, lds, s>>>(P);
     KC_CHECK(hipGetLastError());
     return KC_OK;
 }
@@ -627,12 +644,22 @@ int pivot_reg_launch(const PivLaunch& L, bool mid, hipStream_t s) {
     P.qready = w.qready + static_cast<size_t>(kQueueCap) * queue;
     P.qitems = w.qitems;   // the light launch has ended when the middle one begins; the heavy one has the other region
     P.cancel = L.cancel;
+    constexpr int LW = kRegLightWaves, MW = kRegMidWaves;
+    const int share = mid ? kRegMidShare[L.share] : kRegLightShare[L.share];
     if (mid) {
-        if (L.ec) return L.all ? launch_reg<2, true, true, 16>(P, L.stats, s) : launch_reg<2, true, false, 16>(P, L.stats, s);
-        return L.all ? launch_reg<2, false, true, 16>(P, L.stats, s) : launch_reg<2, false, false, 16>(P, L.stats, s);
+        if (L.ec) return L.all ? launch_reg<2, true, true, MW>(P, L.stats, share, s) : launch_reg<2, true, false, MW>(P, L.stats, share, s);
+        return L.all ? launch_reg<2, false, true, MW>(P, L.stats, share, s) : launch_reg<2, false, false, MW>(P, L.stats, share, s);
     }
-    if (L.ec) return L.all ? launch_reg<1, true, true, 4>(P, L.stats, s) : launch_reg<1, true, false, 4>(P, L.stats, s);
-    return L.all ? launch_reg<1, false, true, 4>(P, L.stats, s) : launch_reg<1, false, false, 4>(P, L.stats, s);
+    if (L.ec) return L.all ? launch_reg<1, true, true, LW>(P, L.stats, share, s) : launch_reg<1, true, false, LW>(P, L.stats, share, s);
+    return L.all ? launch_reg<1, false, true, LW>(P, L.stats, share, s) : launch_reg<1, false, false, LW>(P, L.stats, share, s);
+}
+
+size_t pivot_reg_lds(bool mid, int share, int cu_lds, int* waves) {
+    const size_t block = mid ? reg_block_lds<2, kRegMidWaves>() : reg_block_lds<1, kRegLightWaves>();
+    const int wpb = mid ? kRegMidWaves : kRegLightWaves;
+    const int fit = device_cus() * static_cast<int>(static_cast<size_t>(cu_lds) / block);
+    *waves = div_up(fit, mid ? kRegMidShare[share] : kRegLightShare[share]) * wpb;
+    return block / wpb;
 }
 
 int pivot_leaves_launch(const PivLaunch& L, hipStream_t s) {

@@ -35,7 +35,9 @@ struct Query {
     uint64_t ticket;
     int graph, k, pivot;
     size_t need;
-    size_t lds = 0;     // estimated resident LDS while running
+    size_t lds_alone = 0, lds_shared = 0;   // estimated resident LDS, alone and beside other queries
+    size_t lds = 0;     // as admitted
+    int share = 1;
     double t_submit, t_start = 0, t_done = 0;
     int status = KC_OK;
     kc_u128 count{0, 0};
@@ -111,10 +113,14 @@ struct kc_server {
         while (!pending.empty() && running + static_cast<int>(ready.size()) < slots) {
             kc::Query* q = pending.front();
             const bool alone = running + static_cast<int>(ready.size()) == 0;
-            if (!alone && lds_used + q->lds > lds_total) break;   // wait for on-chip memory
+            const bool shared = !alone || pending.size() > 1;
+            const size_t lds = shared ? q->lds_shared : q->lds_alone;
+            if (!alone && lds_used + lds > lds_total) break;   // wait for on-chip memory
             size_t off = 0;
             if (!arena->alloc(q->need, &off)) break;   // wait for memory (keep arrival order)
-            lds_used += q->lds;
+            q->share = shared ? 2 : 1;
+            q->lds = lds;
+            lds_used += lds;
             q->off = off;
             pending.pop_front();
             ready.push_back(q);
@@ -138,9 +144,11 @@ struct kc_server {
             q->t_start = kc::now_s();
             const kc_dag* d = &dags[q->graph];
             // concurrency comes from the other queries: keep each count on its worker's
-            // stream, and let idle wavefronts leave instead of waiting for handoffs
+            // stream (but for a pivot count's middle list, which would wait for the
+            // heavy one's longest tree), and let idle wavefronts leave instead of waiting
+            // for handoffs
             kc_opts o{};
-            o.flags = KC_OPT_SINGLE_STREAM | KC_OPT_NO_HANDOFF;
+            o.flags = KC_OPT_NO_HANDOFF | (q->pivot ? 0 : KC_OPT_SINGLE_STREAM) | (q->share << kc::kOptShareShift);
             q->status = kc_count(d, q->k, q->pivot, &q->count, arena_mem + q->off, q->need, &o, s);
             q->t_done = kc::now_s();
             {
@@ -199,7 +207,8 @@ extern "C" KC_API int32_t kc_server_submit(kc_server* sv, int32_t graph, int32_t
     q->k = k;
     q->pivot = pivot ? 1 : 0;
     q->need = kc_count_workspace(&sv->dags[graph], k, q->pivot, nullptr);
-    q->lds = kc::count_lds_demand(&sv->dags[graph], k, q->pivot);
+    q->lds_alone = kc::count_lds_demand(&sv->dags[graph], k, q->pivot, 1);
+    q->lds_shared = kc::count_lds_demand(&sv->dags[graph], k, q->pivot, 2);
     q->t_submit = kc::now_s();
     std::lock_guard<std::mutex> lk(sv->mu);
     if (sv->stop) {
