@@ -17,13 +17,13 @@ constexpr int kWidthLists = 6;         // root lists by bitset words per row: 1,
 constexpr int kQueueCap = 16384;        // lane walk: ring slots for subtrees handed between wavefronts (power of 2)
 constexpr int kItemWords = 36;          // queue item: root slot, path length, 2 spare, 32 words of R
 // The lane walk's list 0 has no pair tasks and so no queue; list j >= 1 uses queue
-// j - 1, and the pivot launches of kc_pivot.hip use queues 0 (light) and 1 (heavy).
+// j - 1; the pivot launches use queues 0 (light), 1 (heavy) and 2 (middle).
 constexpr int kQueueLists = kWidthLists - 1;
 constexpr int queue_of(int list) { return list > 0 ? list - 1 : 0; }
 constexpr int kQueueCtlWords = 8;       // per width list: head, tail, pending, rooting, hungry
 // subtree queue control words, and its bounds
 constexpr int Q_HEAD = 0, Q_TAIL = 1, Q_PENDING = 2, Q_ROOTING = 3, Q_HUNGRY = 4;
-constexpr int kMaxWaiters = 256;                            // wavefronts that wait for handed-over work
+constexpr int kMaxWaiters = 256;                            // lane walk: wavefronts that wait for handed-over work
 constexpr unsigned long long kStallTicks = 2000000000ull;   // 20 s at 100 MHz without queue progress
 constexpr int kReadySpins = 1 << 22;                        // wait for a reserved item's sequence word
 constexpr int kQueueCtlTotal = 3 * 8 * 32;   // the most any path uses: three sharded pivot queues
@@ -37,12 +37,9 @@ constexpr int kLaneStealEvery = 16;    // lane walk: wavefront rounds between lo
 constexpr int kLaneStealAfter = 256;   // lane walk: rounds on the current root or subtree before it may hand over
 // pivot: tree nodes between looks at the frame queue, and nodes of the current
 // root or frame before it may hand over.  A consumer re-extracts the frame's
-// root, so only long trees should give work away.  Edge roots with at most 64
-// candidates (the light list) are very many short trees: their frames go only
-// after 65536 nodes; vertex roots and heavy edge roots after 8192.
+// root, so only long trees should give work away.
 constexpr int kPivStealEvery = 64;
 constexpr int kPivStealAfter = 8192;
-constexpr int kPivStealAfterLightEC = 65536;
 // Pivot walks are latency-bound (one wavefront per tree, chains of dependent LDS
 // and global accesses), so more wavefronts may wait for handed-over frames than
 // in the lane walk: 4 per CU.  Dense-core count-all with a 4096-node first
@@ -279,7 +276,7 @@ struct PivLaunch {
     bool all;             // count every size
     bool ec;              // edge roots
     bool stats;
-    bool steal;           // hand saved frames to idle wavefronts (queue regions 0 and 1)
+    bool steal;           // hand saved frames to idle wavefronts
     int share = 0;        // 0: the whole device; a server's query, 1: alone, 2: beside others
     int steal_every = 0;                   // 0: the default (kPivStealEvery)
     int steal_after = 0;                   // 0: the default of the root list and scheme

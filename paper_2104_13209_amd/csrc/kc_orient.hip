@@ -4,7 +4,8 @@
 //   validate  (optional) sorted, simple, symmetric CSR check
 //   key       degree order: key(v) = deg(v)
 //             degeneracy order: key(v) = peeling round of v (k-core removal
-//             order computed by level-synchronous peeling, one cooperative kernel)
+//             order computed by level-synchronous peeling: one cooperative kernel until
+//             few vertices are left, one workgroup for those)
 //   sort      stable LSD radix sort of vertex ids by key: the position in the
 //             sorted order is the new id, so (key, old id) order is the orientation
 //   filter    per vertex, keep neighbours with a larger new id; out-degree
@@ -750,9 +751,6 @@ __device__ int block_exclusive_scan(int x, int* total, int* sh /* >= kBlock/64 +
     return res;
 }
 
-// --------------------------------------------------------- exclusive scan
-
-// Pass 1: per-tile sums.  mode 0: sum of in[]; mode 1: count of radix zeros.
 // ------------------------------------------- approximate degeneracy order
 
 // A relaxation of k-core peeling (an orientation criterion named in Sec. 2;
@@ -969,6 +967,8 @@ __global__ void __launch_bounds__(kBlock) k_cl_round(int r, ClFront f, const int
     }
     if (lane == 0 && mx > 0) atomicMax(&ctl[CTL_MAXKEY], mx);
 }
+
+// --------------------------------------------------------- exclusive scan
 
 // Exclusive scan of a non-negative array, out[count] = total, and its maximum into
 // *top; arrays of up to kScanOne entries by one block, others in three passes.

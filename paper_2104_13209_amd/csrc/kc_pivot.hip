@@ -217,8 +217,8 @@ __global__ void __launch_bounds__(64 * WPB) k_piv(PivParams P) {
     // Termination and the ring protocol are those of the lane walk's subtree
     // queue: a count of wavefronts in the root phase and a count of published,
     // unfinished frames, both read zero (root phase first) when all work is done.
-    constexpr bool CAN_STEAL = 4 + 3 * MAXW <= kItemWords;
-    const bool steal = CAN_STEAL && P.steal && !LOCAL;   // local counts keep each tree on one wavefront
+    constexpr bool CAN_STEAL = !LOCAL && 4 + 3 * MAXW <= kItemWords;   // local counts keep each tree on one wavefront
+    const bool steal = CAN_STEAL && P.steal;
     int* q = P.qctl;
     // an earlier launch of the call stalled or was canceled: give up at once
     if (ld_acquire(P.flags) & (kFlagStalled | kFlagCanceled)) return;
@@ -630,14 +630,15 @@ int pivot_launch(const PivLaunch& L, bool heavy, hipStream_t s) {
     P.gstack = L.w.gstack;
     P.slab_words = L.w.slab_words;
     P.steal = L.steal;
-    P.qctl = L.w.qctl + kQueueCtlWords * (heavy ? 1 : 0);
-    P.qready = L.w.qready + static_cast<size_t>(kQueueCap) * (heavy ? 1 : 0);
-    P.qitems = L.w.qitems + static_cast<size_t>(kQueueCap) * kItemWords * (heavy ? 1 : 0);
+    // queue 1 (the light launches, of per-vertex counts, hand nothing over)
+    P.qctl = L.w.qctl + kQueueCtlWords;
+    P.qready = L.w.qready + kQueueCap;
+    P.qitems = L.w.qitems + static_cast<size_t>(kQueueCap) * kItemWords;
     P.perm = L.perm;
     P.local = L.local;
     const int mode = L.local ? 2 : (L.all ? 1 : 0);
     P.steal_every = L.steal_every > 0 ? L.steal_every : kPivStealEvery;
-    P.steal_after = L.steal_after > 0 ? L.steal_after : (L.ec && !heavy ? kPivStealAfterLightEC : kPivStealAfter);
+    P.steal_after = L.steal_after > 0 ? L.steal_after : kPivStealAfter;
     P.max_waiters = kPivWaitersPerCU * device_cus();
     P.cancel = L.cancel;
     if (!heavy) {

@@ -1,8 +1,8 @@
 """Degeneracy order against a plain level-synchronous peel, vertex by vertex.
 
 The order is (round, id): rounds are fixed by the peeling rule alone, so the whole
-permutation must agree, on both sides of the size (26,000 vertices) up to which one
-workgroup does all of the rounds.
+permutation must agree, on both sides of the size (26,000 vertices) from which the
+whole-device rounds may leave the last ones to one workgroup.
 """
 import numpy as np
 import pytest
