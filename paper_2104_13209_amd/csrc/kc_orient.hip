@@ -56,7 +56,12 @@ constexpr int kStallStart = 1, kStallLater = 2;
 
 // Kernels over rows: a block of 16 wavefronts takes 16 * per rows in runs of `run`
 // consecutive ones (a power of two up to 16 * per).  Short runs spread the hubs, with
-// which vertices ordered by degree or by peeling round end, over the blocks; a batch's
+// which vertices ordered by degree or by peeling round end, over the blocks; longer ones
+// share more cache lines where ids are near their neighbours' (runs of 1 / 4 / 8 / 16, us:
+// k_outdeg and k_fill on the 1M-vertex power-law graph 764 / 712 / 751 / 859, on 3M vertices of
+// mean degree 8 1,159 / 965 / 935 / 920; k_validate on a ring of 200,000 vertices with 80 nearest
+// neighbours 310 / 150 / 150 / 142, on a clique of 5,000 among 100,000 1,466 / 2,016 / 2,281 /
+// 2,667).  A batch's
 // graphs, each with its own hubs, stay together (run = 16 * per: their rows and ranks
 // share cache lines, k_fill 4.6 -> 3.3 ms on the batch of 10,000).  Each wavefront loads the bounds of its `per` rows a lane each
 // and walks rows of up to kLongRow entries four at a time, 16 lanes each: an average
@@ -69,7 +74,8 @@ constexpr int kRowBlock = 1024;
 constexpr int kLongRow = 256;
 constexpr int kBlockRow = 2048;
 constexpr int kMaxPer = 64;
-constexpr int kRowRun = 4;
+constexpr int kRowRun = 8;        // k_outdeg, k_fill
+constexpr int kCheckRun = 4;      // k_validate
 
 struct LongRows {
     int n;
@@ -1710,7 +1716,7 @@ extern "C" KC_API int32_t kc_orient(const kc_csr* g, int32_t order, kc_dag* out,
     // on the way look at the verdict first.
     if (validate) {
         const int per = rows_per_wave(n, nnz);
-        k_validate<<<div_up(n, 16 * per), kRowBlock, 0, s>>>(n, nnz, per, 1, g->row_ptr, g->col, w.ctl);
+        k_validate<<<div_up(n, 16 * per), kRowBlock, 0, s>>>(n, nnz, per, kCheckRun, g->row_ptr, g->col, w.ctl);
         KC_CHECK(hipGetLastError());
     }
     int hctl[CTL_WORDS];
