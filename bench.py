@@ -44,7 +44,8 @@ def log(*a):
 
 
 # sources of the lane-walk launches (kernel, launch set-up, shared device code)
-LANE_SOURCES = ("kc_count.hip", "kc_count_impl.h", "kc_extract.h", "kc_internal.h", "kc_lane.hip", "kc_lane_impl.h")
+LANE_SOURCES = ("kc_classify.h", "kc_count.hip", "kc_count_impl.h", "kc_extract.h", "kc_internal.h", "kc_lane.hip",
+                "kc_lane_impl.h") + tuple("kc_lane_w%d.hip" % w for w in (1, 2, 4, 8, 16, 32))
 
 
 def lane_sources_sha256():

@@ -141,6 +141,10 @@ inline int piv_level_words(int maxw) { return 3 * maxw + 4; }
 // half a claim per wavefront (48 us) where a list is short, and the cap leaves many
 // where it is long.  The head is not looked at before it is claimed from: plain loads
 // of the contended line wait in the same queue (batch of 10,000 graphs: 37 -> 52 ms).
+// A wavefront that is not running yet, as other streams' work holds its compute unit,
+// keeps its first chunk: no other can take it, and the launch ends after it has run.  With
+// four counts at a time (graphs of 100,000 vertices, a thread and a stream each) that costs less
+// than it saves: k = 4 4.9 ms with every root from the head, 1.5 so; pivoting k = 8, 77 and 26.
 //
 // The roots of a chunk lie a chunk count apart.  Lists end with the dense core's
 // roots and batches hold a graph's roots together, so neighbours are heavy together:

@@ -620,11 +620,13 @@ __global__ void __launch_bounds__(kBlock) k_core_rows(const int* __restrict__ ro
 }
 
 // The remaining rounds by one workgroup: degrees and the queue (every vertex once, in
-// order of removal; a round is the segment [head, tail)) are in LDS.  One compute
-// unit's instruction issue bounds it (a round has some 28 rows of 300 entries), so
-// degrees are whole words and rows are padded: an entry costs about five instructions
-// instead of 14 with 16-bit degrees, bounds tests and an early exit each (which
-// took 5.7 ms on the 1M-vertex graph although they held half as many vertices again).
+// order of removal; a round is the segment [head, tail)) are in LDS.  A round has some
+// 28 rows of 300 entries; its latency and the conflicts of its atomics bound it (2.6 ms on
+// the 1M-vertex graph: wavefronts wait on 76% of their cycles, 91% of the LDS cycles
+// are conflicts, 0.28 vector instructions issued per cycle).  Degrees are whole words and rows
+// are padded: an entry costs about five instructions instead of 14 with 16-bit degrees, bounds
+// tests and an early exit each (which took 5.7 ms although they held half as many vertices
+// again).
 __global__ void __launch_bounds__(kPeelBlock) k_core_peel(const CoreSpan* __restrict__ span,
                                                          const unsigned short* __restrict__ rows,
                                                          const int* __restrict__ list, int* round_of, int* key,

@@ -27,8 +27,10 @@
 // density 0.9; 6.0e8 nodes under light roots, 2.1e8 under larger ones), vertex roots,
 // ms: 561 with the LDS rows; 685 with registers and the one queue of before, whose
 // control words bound it; 430 looking at it every 1024 nodes; 136 with eight queues and
-// the smallest frame, looking every 256. Bound now by instruction issue (260 SIMD
-// cycles a node for light roots; 600 for larger ones, at 16 wavefronts per CU).
+// the smallest frame, looking every 256.  Light roots (260 SIMD cycles a node) are bound by
+// scalar issue, 72% of the cycles with vertex roots and 86% with edge roots; larger
+// ones (600) issue vector instructions on 56% and scalar ones on 36%, with 11 of 16 possible wavefronts per
+// CU: each waits for its own chain.
 // Sweep of (nodes between looks, before the first handoff) -> light + heavy ms:
 // (128, 1024) 67 + 88, (256, 1024) 71 + 62, (256, 4096) 64 + 87, (256, 16384) 94 + 145,
 // (1024, 1024) 63 + 74.
