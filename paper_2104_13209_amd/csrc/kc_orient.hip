@@ -294,7 +294,8 @@ constexpr int kCoreCap = 26000;   // 6 bytes of LDS each, of 160 KB
 constexpr int kCoreFront = 96;
 constexpr int kCoreSmall = 4000;  // up to here the one workgroup does all rounds
 constexpr int kCoreLds = 6 * kCoreCap + 8;
-constexpr int kPeelSpins = 1 << 22;
+constexpr int kPeelSpins = 1 << 22;       // polls of the first barrier: seconds
+constexpr int kPeelLaterSpins = 1 << 26;  // of a later one: a minute, far more than a block's longest round
 
 template <class T>
 __device__ __forceinline__ void st_agent(T* p, T v) {
@@ -306,7 +307,8 @@ __device__ __forceinline__ void st_agent(T* p, T v) {
 // are served past the XCDs' L2s, so it is enough that they have been performed
 // (s_waitcnt) when the block arrives; no cache is written back or invalidated.
 // 1.3 us at 64 blocks (cooperative groups: 8.7).  False once a wait ran out, after
-// which every block leaves, and CTL_STALL says so.
+// which every block leaves, and CTL_STALL says so; blocks look at it now and then while
+// they wait.
 __device__ __forceinline__ bool peel_barrier(int* ctl, unsigned int& epoch, int* shared_ok) {
     int* bar = ctl + CTL_BAR;
     __builtin_amdgcn_s_waitcnt(0);
@@ -315,11 +317,14 @@ __device__ __forceinline__ bool peel_barrier(int* ctl, unsigned int& epoch, int*
     if (threadIdx.x == 0) {
         const unsigned int want = epoch * gridDim.x;
         __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int limit = epoch == 1 ? kPeelSpins : kPeelLaterSpins;
         int spins = 0;
-        while (arrivals_missing(static_cast<unsigned int>(ld_acquire(bar)), want) && ++spins < kPeelSpins)
+        while (arrivals_missing(static_cast<unsigned int>(ld_acquire(bar)), want) && ++spins < limit) {
             __builtin_amdgcn_s_sleep(1);
-        *shared_ok = spins < kPeelSpins;
-        if (spins >= kPeelSpins) atomicOr(&ctl[CTL_STALL], epoch == 1 ? kStallStart : kStallLater);
+            if ((spins & 1023) == 0 && ld_acquire(&ctl[CTL_STALL]) != 0) spins = limit - 1;
+        }
+        *shared_ok = spins < limit;
+        if (spins >= limit) atomicOr(&ctl[CTL_STALL], epoch == 1 ? kStallStart : kStallLater);
     }
     __syncthreads();
     return *shared_ok != 0;
