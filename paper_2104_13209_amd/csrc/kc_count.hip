@@ -706,8 +706,8 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             st = side_acquire(&side.s);
             if (st != KC_OK) return st;
             side.held = true;
-            KC_CHECK(hipEventRecord(side.s.fork, s));
-            KC_CHECK(hipStreamWaitEvent(side.s.stream, side.s.fork, 0));
+            st = side.fork(s);
+            if (st != KC_OK) return st;
         }
         for (int lst = top; lst >= 0; lst--) {
             const bool on_side = side.held && lst == top;
@@ -760,8 +760,8 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
             H.timing_ptr = w.acc + 6 + 7 * kWidthLists;   // not part of the list's busy fraction
             st = lane_launch(H, s);
             if (st != KC_OK) return st;
-            KC_CHECK(hipEventRecord(side.s.join, side.s.stream));
-            KC_CHECK(hipStreamWaitEvent(s, side.s.join, 0));
+            st = side.join(s);
+            if (st != KC_OK) return st;
         }
         if (prof && top < 1) KC_CHECK(hipEventRecord(pe->ev[2], s));
         if (prof)
@@ -847,8 +847,8 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
                 if (st != KC_OK) return st;
                 side.held = true;
                 ms = side.s.stream;
-                KC_CHECK(hipEventRecord(side.s.fork, s));
-                KC_CHECK(hipStreamWaitEvent(ms, side.s.fork, 0));
+                st = side.fork(s);
+                if (st != KC_OK) return st;
             }
             if (dm > kLightCap) {
                 st = pivot_reg_launch(L, true, ms);
@@ -859,8 +859,8 @@ int run_count(const kc_dag* d, int k, int pivot_all, const kc_opts* o, const Cou
                 if (st != KC_OK) return st;
             }
             if (side.held) {
-                KC_CHECK(hipEventRecord(side.s.join, ms));
-                KC_CHECK(hipStreamWaitEvent(s, side.s.join, 0));
+                st = side.join(s);
+                if (st != KC_OK) return st;
             }
             st = pivot_leaves_launch(L, s);
             if (st != KC_OK) return st;

@@ -49,12 +49,26 @@ struct SideStream {
 int side_acquire(SideStream* out);      // KC_OK or KC_EDEVICE
 void side_release(const SideStream& s);
 
-// Returns a held side stream to the pool at scope exit.
+// Returns a held side stream to the pool at scope exit.  Work that has been forked onto it and
+// not joined, because a later launch failed, is waited for: it uses the caller's workspace.
 struct SideGuard {
     SideStream s;
-    bool held = false;
+    bool held = false, forked = false;
     ~SideGuard() {
+        if (forked) (void)hipStreamSynchronize(s.stream);
         if (held) side_release(s);
+    }
+    int fork(hipStream_t from) {
+        KC_CHECK(hipEventRecord(s.fork, from));
+        KC_CHECK(hipStreamWaitEvent(s.stream, s.fork, 0));
+        forked = true;
+        return KC_OK;
+    }
+    int join(hipStream_t to) {
+        KC_CHECK(hipEventRecord(s.join, s.stream));
+        KC_CHECK(hipStreamWaitEvent(to, s.join, 0));
+        forked = false;
+        return KC_OK;
     }
 };
 
